@@ -838,11 +838,9 @@ struct PruneLds {
   uint64_t* keys2;  // [rows] survivors in order
   uint8_t* vec;     // [rows * vstride] staged candidate vectors (uint8 rows)
   uint32_t* norm;   // [rows]
-  uint32_t* idx;    // [rows] alive-candidate list (FP32 rows)
-  uint8_t* kill;    // [rows] per-candidate prune flags (FP32 rows)
   uint32_t* out_ids;  // [R]
   uint32_t* out_d;    // [R] stored distances (uint32 for uint8 rows, FP32 bits for float)
-  // matrix-core selection (uint8 rows; vec, norm and idx are then not carved):
+  // matrix-core selection (uint8 rows; vec and norm are then not carved):
   uint32_t* M;   // [64 * 63 / 2 + 1] distances between the candidates of one tile; null: staged rows
   uint32_t* tn;  // [64] shifted squared norms of the tile's candidates
   uint32_t* kn;  // [R] shifted squared norms of the kept candidates

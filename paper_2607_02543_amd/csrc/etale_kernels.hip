@@ -1765,7 +1765,7 @@ __device__ inline MaintLds carve(char* base, const MaintArgs& a, uint32_t R) {
   p += (size_t)a.prune_cap * 8;
   m.pr.M = m.pr.tn = m.pr.kn = nullptr;
   m.pr.vec = nullptr;
-  m.pr.norm = m.pr.idx = nullptr;
+  m.pr.norm = nullptr;
   if (a.mx) {  // the matrix-core selection: a distance table instead of staged rows
     p = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(p) + 15u) & ~(uintptr_t)15u);
     m.pr.M = reinterpret_cast<uint32_t*>(p);
@@ -1779,8 +1779,6 @@ __device__ inline MaintLds carve(char* base, const MaintArgs& a, uint32_t R) {
     p += (size_t)a.prune_cap * a.vstride;
     m.pr.norm = reinterpret_cast<uint32_t*>(p);
     p += (size_t)a.prune_cap * 4;
-    m.pr.idx = reinterpret_cast<uint32_t*>(p);
-    p += (size_t)a.prune_cap * 4;
   }
   m.pr.out_ids = reinterpret_cast<uint32_t*>(p);
   p += (size_t)(R + 1) * 4;
@@ -1793,8 +1791,6 @@ __device__ inline MaintLds carve(char* base, const MaintArgs& a, uint32_t R) {
   m.nl_d = reinterpret_cast<uint32_t*>(p);
   p += (size_t)(R + 1) * 4;
   m.tmp = reinterpret_cast<uint32_t*>(p);
-  p += (size_t)(R + 1) * 4;
-  m.pr.kill = reinterpret_cast<uint8_t*>(p);
   return m;
 }
 
@@ -2053,12 +2049,14 @@ __device__ inline int prune_select_mx(const Index& ix, int m, PruneLds& s) {
 }
 
 // ---- per-metric maintenance policy --------------------------------------------------------
-// prune: RobustPrune; dist1: the exact stored distance between two rows (the
+// prune: RobustPrune (KNOWN: the caller may leave the keys of its first nk
+// candidates in s.keys, where their distances are already stored); dist1: the
+// exact stored distance between two rows (the
 // bit pattern kept in a slab); kd: a stored distance as the distance half of a
 // (distance, id) key.
 template <int G>
 struct MaintU8 {
-  __device__ static int prune(const Index& ix, uint32_t p, const uint32_t* cand, int n, PruneLds& s) {
+  __device__ static int prune(const Index& ix, uint32_t p, const uint32_t* cand, int n, PruneLds& s, int = 0) {
     if constexpr (G <= 8) {
       if (s.M) return prune_select_mx<G>(ix, prune_rank_u8<G>(ix, p, cand, n, s), s);
     }
@@ -2074,20 +2072,24 @@ struct MaintU8 {
     return key_dist(ck[0]);
   }
   __device__ static uint32_t kd(uint32_t rho) { return rho; }
-  static constexpr bool CHAIN = true;  // reverse edges keep a cached candidate state
+  static constexpr bool CHAIN = true;   // reverse edges keep a cached candidate state
+  static constexpr bool KNOWN = false;  // every prune ranks from the rows
+  static constexpr unsigned WPE = 3;    // waves per SIMD of the forward and refine kernels
   static constexpr int GL = G;
 };
 
 template <int G>
 struct MaintF32 {
-  __device__ static int prune(const Index& ix, uint32_t p, const uint32_t* cand, int n, PruneLds& s) {
-    return robust_prune_f32<G>(ix, p, cand, n, s);
+  __device__ static int prune(const Index& ix, uint32_t p, const uint32_t* cand, int n, PruneLds& s, int nk = 0) {
+    return robust_prune_f32<G>(ix, p, cand, n, s, nk);
   }
   __device__ static uint32_t dist1(const Index& ix, uint32_t w, uint32_t v, uint32_t*, uint64_t*) {
     return dist1_f32<G>(ix, w, v);
   }
   __device__ static uint32_t kd(uint32_t rho) { return fkey(__builtin_bit_cast(float, rho)); }
   static constexpr bool CHAIN = false;
+  static constexpr bool KNOWN = true;
+  static constexpr unsigned WPE = 2;  // a block's eight rows in registers: 168 of them would spill
   static constexpr int GL = G;
 };
 
@@ -2120,7 +2122,7 @@ __device__ inline void forward_one(const Index& ix, const MaintArgs& a, MaintLds
 }
 
 template <class P>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_forward(Index ix, MaintArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P::WPE))) k_forward(Index ix, MaintArgs a) {
   extern __shared__ __align__(16) char smem[];
   if (gated(ix, a.d)) return;
   resolve(ix, a);
@@ -2179,6 +2181,16 @@ __global__ void __launch_bounds__(256) k_segments(Index ix, const uint64_t* pair
   for (uint32_t i = threadIdx.x; i < cnt_s; i += blockDim.x) seg[base_s + i] = buf[i];
 }
 
+// the current list as a prune's first n candidates, with their known distances
+template <class P>
+__device__ inline void known_list(const MaintLds& m, uint32_t n) {
+  const uint32_t l = (uint32_t)lane_id();
+  if (l < n) {
+    m.cand[l] = m.nl_id[l];
+    if constexpr (P::KNOWN) m.pr.keys[l] = make_key(P::kd(m.nl_d[l]), m.nl_id[l]);
+  }
+}
+
 // ---- insert: reverse edges in (target, source) order, one publication per target ------
 template <class P>
 __device__ inline void reverse_one(const Index& ix, const MaintArgs& a, MaintLds& m, uint32_t t, SlabCursor& cur) {
@@ -2213,10 +2225,10 @@ __device__ inline void reverse_one(const Index& ix, const MaintArgs& a, MaintLds
       wave_sync();
       ++n;
     } else {
-      if ((uint32_t)l < n) m.cand[l] = m.nl_id[l];
+      known_list<P>(m, n);
       if (l == 0) m.cand[n] = v;
       wave_sync();
-      n = (uint32_t)P::prune(ix, w, m.cand, (int)n + 1, m.pr);
+      n = (uint32_t)P::prune(ix, w, m.cand, (int)n + 1, m.pr, P::KNOWN ? (int)n : 0);
       copy_out(m, n);
     }
   }
@@ -2693,10 +2705,10 @@ __global__ void __launch_bounds__(256) k_reverse_fast(Index ix, MaintArgs a) {
         wave_sync();
         ++n;
       } else {
-        if ((uint32_t)l < n) m.cand[l] = m.nl_id[l];
+        known_list<P>(m, n);
         if (l == 0) m.cand[n] = v;
         wave_sync();
-        n = (uint32_t)P::prune(ix, w, m.cand, (int)n + 1, m.pr);
+        n = (uint32_t)P::prune(ix, w, m.cand, (int)n + 1, m.pr, P::KNOWN ? (int)n : 0);
         copy_out(m, n);
       }
       done = publish_once(ix, w, snap, m.nl_id, m.nl_d, n, C_PUB_REVERSE);
@@ -2787,7 +2799,7 @@ __device__ inline void refine_one(const Index& ix, const MaintArgs& a, MaintLds&
 // are computed into the insert searches' scratch first (k_refine), then
 // published (k_refine_publish).
 template <class P>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_refine(Index ix, MaintArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P::WPE))) k_refine(Index ix, MaintArgs a) {
   extern __shared__ __align__(16) char smem[];
   if (gated(ix, a.d)) return;
   resolve(ix, a);
@@ -2978,10 +2990,17 @@ __device__ inline void repair_one(const Index& ix, const MaintArgs& a, MaintLds&
     const uint32_t nk = (uint32_t)__popcll(km);
     uint32_t kid = (l < kc) ? m.pr.out_ids[l] : NONE;
     wave_sync();
-    if (keep) m.cand[lanes_below(km)] = m.nl_id[l];
-    if (l < kc) m.cand[nk + (uint32_t)l] = kid;
+    // both parts' distances to a are known: the list's are stored, K's were just computed
+    if (keep) {
+      m.cand[lanes_below(km)] = m.nl_id[l];
+      if constexpr (P::KNOWN) m.pr.keys[lanes_below(km)] = make_key(P::kd(m.nl_d[l]), m.nl_id[l]);
+    }
+    if (l < kc) {
+      m.cand[nk + (uint32_t)l] = kid;
+      if constexpr (P::KNOWN) m.pr.keys[nk + (uint32_t)l] = make_key(P::kd(m.pr.out_d[l]), kid);
+    }
     wave_sync();
-    n = (uint32_t)P::prune(ix, an, m.cand, (int)(nk + (uint32_t)kc), m.pr);
+    n = (uint32_t)P::prune(ix, an, m.cand, (int)(nk + (uint32_t)kc), m.pr, P::KNOWN ? (int)(nk + (uint32_t)kc) : 0);
     copy_out(m, n);
   }
   publish(ix, an, m.nl_id, m.nl_d, n, C_PUB_REPAIR, &cur);
@@ -4535,9 +4554,9 @@ uint32_t pool_lds_per_wave(uint32_t vstride) { return pool_lds_bytes(vstride); }
 
 uint32_t maint_lds_per_wave(const MaintArgs& a, uint32_t R) {
   const size_t sel = a.mx ? 16 + (size_t)MX_M_WORDS * 4 + 2 * 64 * 4  // alignment, table, tile and kept norms
-                          : (size_t)a.prune_cap * a.vstride + (size_t)a.prune_cap * 8;  // staged rows, norms
+                          : (size_t)a.prune_cap * a.vstride + (size_t)a.prune_cap * 4;  // staged rows, norms
   size_t b = (size_t)a.nsort * 8 + (size_t)a.prune_cap * 8 + sel + (size_t)(R + 1) * 8 + (size_t)a.nmax * 4 +
-             (size_t)(R + 1) * 12 + (size_t)a.prune_cap;
+             (size_t)(R + 1) * 12;
   return (uint32_t)((b + 15) & ~(size_t)15);
 }
 
