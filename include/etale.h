@@ -96,7 +96,8 @@ typedef struct {
   uint32_t tombstone_only;   /* 1: delete only flags; no repair, no reclaim */
   uint32_t publish_attempts; /* CAS attempt budget of one publication */
   uint32_t max_batch;        /* largest insert / delete batch of one call */
-  uint32_t vt_slots;         /* visited-table slots per search (power of two) */
+  uint32_t vt_slots;         /* visited-table slots per search (power of two); a launch may
+                                take more, up to 4096, where the chip has room for them */
   uint32_t waves_per_block;  /* search wavefronts per workgroup */
   int32_t metric;            /* ETALE_METRIC_* */
   int32_t traversal;         /* ETALE_TRAV_* (float metric only) */

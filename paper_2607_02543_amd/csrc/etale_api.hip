@@ -213,6 +213,32 @@ uint32_t search_waves_per_block(const etale_index* ix, uint32_t lds_per_wave) {
   return w;
 }
 
+// Visited-table slots of a search launch over nq queries: at least the
+// configured count, and up to 4,096 (results do not depend on it) where more
+// cost nothing or pay for themselves.
+// - Float rows: the largest power of two up to (L + 2) R, the ids a search
+//   offers when its neighborhoods hardly overlap (embeddings spread over the
+//   sphere). A table that fills up makes every further id a repeated distance
+//   and a check for repeats; registers, not LDS, bound the resident waves.
+//   3,001 queries, 96-d, L = 64, R = 32: 562 us at 1,024 slots, 483 at 2,048,
+//   496 at 4,096, 595 at 8,192; 2,000 queries, 768-d FP8, L = 96, R = 48:
+//   1,600 / 1,390 / 1,070 / 1,590.
+// - Launches whose waves all fit the chip's LDS with twice the slots, up to
+//   twice those ids: a sparse table settles almost every id on its first try
+//   (a step's 64 ids: 3,700 -> 1,430 cycles at 96-d float, 1,700 -> 900 at
+//   uint8). Where the waves are bound by LDS the configured count stays:
+//   10,000 uint8 queries take 383 us at 1,024 slots and 450 at 2,048.
+constexpr uint32_t VT_MAX = 4096;
+constexpr uint64_t CHIP_LDS = 256ull * 160 * 1024;
+uint32_t search_vt_slots(const etale_index* ix, uint32_t L, uint64_t nq) {
+  uint32_t v = ix->cfg.vt_slots;
+  const uint64_t ids = (uint64_t)(L + 2) * ix->cfg.R;
+  if (ix->cfg.metric == ETALE_METRIC_IP_F32)
+    while (v < VT_MAX && 2 * v <= ids) v *= 2;
+  while (v < VT_MAX && v <= ids && nq * search_lds_per_wave(L, 2 * v, ix->cfg.W) <= CHIP_LDS) v *= 2;
+  return v;
+}
+
 constexpr uint32_t SCAN_L_MAX = 256;
 
 uint32_t maint_waves_per_block(const MaintArgs& a) {
@@ -358,9 +384,10 @@ etale_status run_searches(etale_index* ix, int mode, const uint8_t* q, uint64_t 
     sa.L = L;
     sa.k = k;
     sa.vcap = vcap;
-    sa.vt_mask = ix->cfg.vt_slots - 1;
+    const uint32_t vt = search_vt_slots(ix, L, cn);
+    sa.vt_mask = vt - 1;
     sa.W = ix->cfg.W;
-    sa.lds_per_wave = search_lds_per_wave(L, ix->cfg.vt_slots, ix->cfg.W);
+    sa.lds_per_wave = search_lds_per_wave(L, vt, ix->cfg.W);
     sa.init_keys = scr.keys;
     sa.init_n = scr.n;
     sa.init_stride = L;

@@ -313,6 +313,12 @@ __device__ inline uint32_t group_sum(uint32_t v) {
 constexpr int VT_BUCKETS = 2;  // buckets looked at per id (8 slots)
 enum VtResult : uint32_t { VT_SEEN = 0, VT_NEW = 1, VT_CROWDED = 2 };
 
+// empty table (a power of two of slots, 64 or more; 16-byte aligned)
+__device__ inline void vt_clear(uint32_t* vt, uint32_t mask) {
+  for (uint32_t i = 4u * (uint32_t)lane_id(); i <= mask; i += 256)
+    *reinterpret_cast<uint4*>(vt + i) = make_uint4(NONE, NONE, NONE, NONE);
+}
+
 __device__ inline uint32_t vt_insert(uint32_t* vt, uint32_t mask, uint32_t id) {
   const uint32_t bmask = (mask + 1u) / 4u - 1u;
   const uint32_t b = (id * 2654435761u) & bmask;

@@ -1270,7 +1270,7 @@ __device__ inline void search_one(const Index& ix, const SearchArgs& a, char* ba
   const void* qrow = a.mode == MODE_QUERY ? (const void*)((const uint8_t*)a.q + (size_t)qi * TP::query_bytes(ix))
                                           : TP::stored_row(ix, a.first + qi);
   const typename TP::Q qv = TP::load_query(qrow);
-  for (uint32_t i = (uint32_t)l; i <= a.vt_mask; i += 64) vt[i] = NONE;
+  vt_clear(vt, a.vt_mask);
   // the initial list: the L best start nodes, with their reference words
   const uint32_t n0 = a.init_n[qi];
   for (uint32_t i = (uint32_t)l; i < n0; i += 64) {
@@ -1446,7 +1446,7 @@ __device__ inline void search_one_rl(const Index& ix, const SearchArgs& a, char*
   const void* qrow = a.mode == MODE_QUERY ? (const void*)((const uint8_t*)a.q + (size_t)qi * TP::query_bytes(ix))
                                           : TP::stored_row(ix, a.first + qi);
   const typename TP::Q qv = TP::load_query(qrow);
-  for (uint32_t i = (uint32_t)l; i <= a.vt_mask; i += 64) vt[i] = NONE;
+  vt_clear(vt, a.vt_mask);
   // the initial list: the L best start nodes, with their reference words
   int n = (int)a.init_n[qi];
   uint64_t lk[NL], lr[NL];
