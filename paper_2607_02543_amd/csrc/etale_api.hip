@@ -44,7 +44,7 @@ struct etale_index {
   uint64_t* pairs_b = nullptr;
   uint32_t* dlist = nullptr;
   uint32_t* dirty = nullptr;
-  uint64_t* bitmap = nullptr;
+  unsigned long long* bitmap = nullptr;  // deletion flags, one bit per id
   uint32_t* seg = nullptr;        // run starts of a sorted pair list
   uint32_t* hist = nullptr;       // radix-sort digit counts
   int32_t* status = nullptr;      // round status words of the calls that do not take one
@@ -463,13 +463,12 @@ etale_status enqueue_reclaim(etale_index* ix, uint64_t n_ids_max, int32_t* statu
   Dyn dn;
   dn.skip = G_FAIL;
   dn.n_ctr = C_NEXT_ID;
-  HIP_TRY(launch_del_bitmap(d, n_ids_max, dn, ix->bitmap, ix->stream));
-  HIP_TRY(launch_dirty(d, n_ids_max, dn, ix->bitmap, ix->dirty, ix->stream));
+  HIP_TRY(launch_dirty(d, n_ids_max, dn, ix->dirty, ix->stream));
   HIP_TRY(launch_reclaim_gate(d, status, ix->stream));
   Dyn dc;
   dc.skip = G_FAIL | G_RFAIL;
   dc.n_ctr = C_DIRTY;
-  HIP_TRY(launch_compact(d, ix->dirty, n_ids_max, dc, ix->bitmap, ix->stream));
+  HIP_TRY(launch_compact(d, ix->dirty, n_ids_max, dc, ix->stream));
   Dyn df;
   df.skip = G_FAIL | G_RFAIL;
   df.n_ctr = C_NEXT_ID;
@@ -494,7 +493,7 @@ etale_status enqueue_round(etale_index* ix, const RoundPlan& p) {
     HIP_TRY(launch_sort(d, ix->pairs_a, ix->pairs_b, p.max_d, dd, 32, 32, ix->hist, s, &sorted));
     HIP_TRY(launch_del_classify(d, sorted, p.max_d, dd, p.del_status, ix->dlist, s));
   }
-  HIP_TRY(launch_round_gate(d, ix->cfg.tombstone_only, BOOT_MAX, p.status, s));
+  HIP_TRY(launch_round_gate(d, ix->cfg.tombstone_only, BOOT_MAX, p.status, s, p.reclaim));
   if (p.max_d) {
     Dyn dt;
     dt.skip = G_FAIL;
@@ -572,6 +571,7 @@ etale_status enqueue_round(etale_index* ix, const RoundPlan& p) {
         pool_lds_per_wave(pa.vstride) <= 65536u) {
       pa.chain = 1;
       pa.lds_per_wave = pool_lds_per_wave(pa.vstride);  // the pool kernel carves only the pool
+      if (ix->cfg.dim <= 128 && d.cmp29) pa.slow = reinterpret_cast<uint32_t*>(sorted == ix->pairs_a ? ix->pairs_b : ix->pairs_a);
     }
     pa.np_ctr = C_R_NDEL;
     pa.np_mult = R;
@@ -609,6 +609,7 @@ etale_status enqueue_round(etale_index* ix, const RoundPlan& p) {
       // reads rows from memory and stages none
       if (ix->cfg.dim <= 128) ra.vstride = 0;
       ra.lds_per_wave = chain_lds_per_wave(R, ra.vstride);
+      if (ix->cfg.dim <= 128 && d.cmp29) ra.slow = reinterpret_cast<uint32_t*>(sorted == ix->pairs_a ? ix->pairs_b : ix->pairs_a);
     }
     ra.n = p.max_i;
     ra.pairs = sorted;
@@ -766,6 +767,7 @@ etale_status etale_create(const etale_config* cfg, etale_t* out) {
     const uint64_t dmax = (uint64_t)c.dim * 255u * 255u;  // largest uint8 squared distance
     d.cmp32 = c.metric == ETALE_METRIC_L2_U8 && dmax < (1ull << 24) && d.a2 < (1u << 24) && d.b2 < (1u << 24) &&
               (uint64_t)std::max(d.a2, d.b2) * dmax < (1ull << 32);
+    d.cmp29 = d.cmp32 && (uint64_t)std::max(d.a2, d.b2) * dmax < (1ull << 29);
   }
   d.publish_attempts = c.publish_attempts;
   d.fence = 0;  // every call is a round-synchronous launch sequence
@@ -789,6 +791,7 @@ etale_status etale_create(const etale_config* cfg, etale_t* out) {
   d.retired_stack = ix->retired_stack;
   d.ctr = ix->ctr;
   d.entries = ix->entries;
+  d.delbits = ix->bitmap;
   d.ent_x = ix->ent_x;
   d.ent_norm = ix->ent_norm;
   ix->pair_bits = 1;
@@ -906,7 +909,7 @@ etale_status etale_reclaim(etale_t ix) {
   CHECK_HANDLE();
   if (ix->cfg.tombstone_only) return ETALE_OK;
   if (etale_status st = refresh_mirror(ix)) return st;
-  HIP_TRY(launch_round_begin(ix->dev, nullptr, 0, 0, 0, 0, 0, 0, ix->status, ix->stream));
+  HIP_TRY(launch_round_begin(ix->dev, nullptr, 0, 0, 0, 0, 0, 0, ix->status, ix->stream, true));
   if (etale_status st = enqueue_reclaim(ix, ix->next_id, ix->status)) return st;
   return round_status(ix, "reclaim");
 }

@@ -74,6 +74,7 @@ enum Counter {
   C_QDONE,     // waves of that launch that have left the queue
   C_RES_FREE,  // a launch's slab reservation: free-stack top before it (~0: none)
   C_RES_RET,   // and its first retired-stack slot (~0: none)
+  C_NSLOW,     // targets of a maintenance phase left to its general kernel
   C_NCOUNTERS = 32
 };
 // the repair launch's work queues, each on a line of its own after the
@@ -92,6 +93,7 @@ struct Index {
   uint32_t dim, R;
   uint32_t a2, b2;  // alpha = a/b, applied squared: a^2 * D1 <= b^2 * D2
   uint32_t cmp32;   // 1: uint8 distances and both products stay below 2^32 (24-bit multiplies suffice)
+  uint32_t cmp29;   // 1: and both products below 2^29 (room for the cover test's markers)
   uint32_t publish_attempts;
   uint32_t fence;   // 1: a release fence orders a slab's contents before its reference (concurrent readers)
   uint32_t concurrent;  // 1: searches may run alongside writers: slab ids are read with agent-coherent loads
@@ -111,6 +113,7 @@ struct Index {
   uint32_t* retired_stack;
   unsigned long long* ctr;
   uint32_t* entries;
+  unsigned long long* delbits;  // one bit per id: its deletion flag, for the tests that need nothing else of the word
   uint8_t* ent_x;     // uint8 rows: the entry set's rows, each byte XOR 0x80, in matrix-operand order
   int32_t* ent_norm;  // minus their squared norms (as signed bytes), padded to a multiple of 64
 };
@@ -198,6 +201,11 @@ __device__ inline uint64_t load_ref(const Index& ix, uint32_t u) {
   return __hip_atomic_load(&ix.refs[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Whether id is flagged: the flag's copy in the dense bitmap (1/64 of the
+// reference words, so it stays in L2), set with the flag and like it for good.
+// Maintenance phases only: a search's state may be an older snapshot.
+__device__ inline bool del_bit(const Index& ix, uint32_t id) { return (ix.delbits[id >> 6] >> (id & 63u)) & 1ull; }
+
 // ---- uint8 squared L2 via 4-wide byte dot products ----------------------------
 // |a-b|^2 = |a|^2 + |b|^2 - 2<a,b>, every term exact in 32-bit integers for
 // dim <= 1024 (1024 * 255^2 < 2^31).
@@ -211,8 +219,8 @@ __device__ inline uint32_t dot16(uint4 a, uint4 b, uint32_t acc) {
 }
 
 // The value of lane l ^ J. Distances within a row of 16 lanes move by DPP
-// (quad permutes, row shifts and rotates: ALU latency, no LDS crossbar);
-// 16 and 32 go through ds_bpermute.
+// (quad permutes, row shifts and rotates), 16 and 32 by the lane swaps: ALU
+// latency, no LDS crossbar.
 template <int J>
 __device__ inline uint32_t lane_xor(uint32_t v) {
   static_assert(J == 1 || J == 2 || J == 4 || J == 8 || J == 16 || J == 32, "lane distance");
@@ -226,8 +234,12 @@ __device__ inline uint32_t lane_xor(uint32_t v) {
     return (threadIdx.x & 4u) ? dn : up;
   } else if constexpr (J == 8) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false);  // row_ror:8
+  } else if constexpr (J == 16) {  // an even row of 16 lanes gets (own, partner's), an odd one (partner's, own)
+    const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (threadIdx.x & 16u) ? s[0] : s[1];
   } else {
-    return (uint32_t)__shfl_xor((int)v, J, 64);
+    const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (threadIdx.x & 32u) ? s[0] : s[1];
   }
 }
 template <int J>
@@ -279,6 +291,20 @@ __device__ inline void wave_sort_regs(uint64_t (&v)[NK]) {
     bitonic_pass_regs<K, K / 2, NK>(v);
     wave_sort_regs<NK, K * 2>(v);
   }
+}
+
+// The same for one 32-bit key per lane (64 of them).
+template <int K, int J>
+__device__ inline void bitonic32_step(uint32_t& v) {
+  const int l = lane_id();
+  const uint32_t p = lane_xor<J>(v);
+  v = ((l & J) == 0) == ((l & K) == 0) ? min(v, p) : max(v, p);
+  if constexpr (J > 1) bitonic32_step<K, J / 2>(v);
+}
+template <int K = 2>
+__device__ inline void wave_sort32(uint32_t& v) {
+  bitonic32_step<K, K / 2>(v);
+  if constexpr (K < 64) wave_sort32<K * 2>(v);
 }
 
 // sum over the G consecutive lanes of a group (G a power of two), every lane
@@ -903,20 +929,20 @@ __device__ inline int prune_rank_u8(const Index& ix, uint32_t p, const uint32_t*
   const uint32_t pp = group_sum<G>(dot16(pf, pf, 0u));
   const int np = next_pow2_ge64(n);
   // 1. keys (D(p,c), c) for admissible candidates; a candidate's row and its
-  // reference word (for the flag) are read together
+  // flag are read together
   for (int base = 0; base < np; base += 4 * VPP) {
     uint4 v[4];
     uint32_t id[4];
-    uint64_t rf[4];
+    bool del[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       int vi = base + u * VPP + grp;
       id[u] = vi < n ? cand[vi] : NONE;
       if (id[u] == p) id[u] = NONE;
       v[u] = make_uint4(0, 0, 0, 0);
-      rf[u] = 0;
+      del[u] = false;
       if (id[u] != NONE) {
-        rf[u] = load_ref(ix, id[u]);
+        del[u] = del_bit(ix, id[u]);
         v[u] = reinterpret_cast<const uint4*>(ix.x + (size_t)id[u] * ix.dim)[c];
       }
     }
@@ -925,7 +951,7 @@ __device__ inline int prune_rank_u8(const Index& ix, uint32_t p, const uint32_t*
       uint32_t px = group_sum<G>(dot16(pf, v[u], 0u));
       uint32_t xx = group_sum<G>(dot16(v[u], v[u], 0u));
       int vi = base + u * VPP + grp;
-      const bool none = id[u] == NONE || ref_del(rf[u]);
+      const bool none = id[u] == NONE || del[u];
       if (c == 0 && vi < np) s.keys[vi] = none ? KEY_NONE : make_key(pp + xx - 2u * px, id[u]);
     }
   }

@@ -300,11 +300,11 @@ __device__ inline int robust_prune_f32(const Index& ix, uint32_t p, const uint32
   const int l = lane_id();
   const int grp = l / G, i8 = l & 7;
   const int np = next_pow2_ge64(n);
-  // 1. keys: flags first (64 candidates' words in flight together), then the
+  // 1. keys: flags first (64 candidates' in flight together), then the
   // distances not known yet, 8 x VPP rows in flight together
   for (int i = l; i < np; i += 64) {
     const uint32_t id = i < n ? cand[i] : NONE;
-    const bool drop = id == NONE || id == p || ref_del(load_ref(ix, id));
+    const bool drop = id == NONE || id == p || del_bit(ix, id);
     if (drop) s.keys[i] = KEY_NONE;
     else if (i >= nk) s.keys[i] = 0;
   }

@@ -26,6 +26,8 @@ __global__ void k_init(Index ix) {
     ix.refs[i] = REF_UNBORN;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ix.P; i += stride)
     ix.free_stack[i] = (uint32_t)(ix.P - 1 - i);
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (ix.cap + 63) / 64; i += stride)
+    ix.delbits[i] = 0;
   if (blockIdx.x == 0)
     for (uint32_t i = threadIdx.x; i < CTR_WORDS; i += blockDim.x) ix.ctr[i] = i == C_FREE_TOP ? ix.P : 0ull;
 }
@@ -58,8 +60,9 @@ __global__ void k_recycle_commit(Index ix) {
 constexpr int32_t ST_EINVAL = -1, ST_EPOOL = -3, ST_ECAPACITY = -4;
 
 __global__ void k_round_begin(Index ix, const uint32_t* counts, uint32_t nd, uint32_t ni, uint32_t nq,
-                              uint32_t max_d, uint32_t max_i, uint32_t max_q, int32_t* status) {
+                              uint32_t max_d, uint32_t max_i, uint32_t max_q, int32_t* status, uint32_t reclaim) {
   if (threadIdx.x != 0) return;
+  if (reclaim) ix.ctr[C_DIRTY] = ix.ctr[C_DEAD] = 0;  // a reclaim alone: nothing gates it before
   if (counts) {
     nd = counts[0];
     ni = counts[1];
@@ -88,7 +91,7 @@ __global__ void k_round_begin(Index ix, const uint32_t* counts, uint32_t nd, uin
 // the worst-case slab demand |I|(R+2) + |D|R (|I|(R+2) without repair); a
 // bootstrap (no live node left once this round's tombstones are set) takes at
 // most boot_max new vectors. On success the new ids are handed out.
-__global__ void k_round_gate(Index ix, uint32_t tombstone_only, uint32_t boot_max, int32_t* status) {
+__global__ void k_round_gate(Index ix, uint32_t tombstone_only, uint32_t boot_max, int32_t* status, uint32_t reclaim) {
   if (threadIdx.x != 0) return;
   uint64_t gate = ix.ctr[C_R_GATE];
   if (gate & G_FAIL) return;
@@ -110,6 +113,7 @@ __global__ void k_round_gate(Index ix, uint32_t tombstone_only, uint32_t boot_ma
     ix.ctr[C_R_FIRST] = next;
     ix.ctr[C_NEXT_ID] = next + ni;
     ix.ctr[C_LIVE] = live - dok + ni;
+    if (reclaim) ix.ctr[C_DIRTY] = ix.ctr[C_DEAD] = 0;
   }
   ix.ctr[C_R_GATE] = gate;
   if (status) status[0] = st;
@@ -2452,7 +2456,7 @@ __device__ inline void chain_first_mx(const Index& ix, const ChainLds& c, uint32
   const int l = lane_id();
   const uint32_t r = (uint32_t)(l & 15), kc = (uint32_t)(l >> 4) * 16u, rb = (uint32_t)(l >> 4) * 4u;
   const bool need = (uint32_t)l < S && !((known >> l) & 1ull);
-  const uint64_t ref = need ? load_ref(ix, c.id[l]) : 0ull;
+  const bool del = need && del_bit(ix, c.id[l]);
   v4i32 f[3][KS];
 #pragma unroll
   for (int h = 0; h < 3; ++h) {
@@ -2490,7 +2494,7 @@ __device__ inline void chain_first_mx(const Index& ix, const ChainLds& c, uint32
       }
     }
   }
-  if (need) c.dead[l] = ref_del(ref);
+  if (need) c.dead[l] = del;
   wave_sync();
 }
 
@@ -2570,7 +2574,7 @@ __device__ inline void reverse_chain_u8(const Index& ix, const MaintArgs& a, con
         const uint64_t nm = ballot(need);
         if (need) {
           c.out_id[lanes_below(nm)] = sl;
-          c.dead[sl] = ref_del(load_ref(ix, c.id[sl]));
+          c.dead[sl] = del_bit(ix, c.id[sl]);
         }
         wave_sync();
         chain_stage_rows<G>(ix, c, c.out_id, __popcll(nm));
@@ -2717,14 +2721,49 @@ __global__ void __launch_bounds__(256) k_reverse_fast(Index ix, MaintArgs a) {
   }
 }
 
+// The slabs k_reserve_launch reserved for a launch: one fresh slab and one
+// retired slot per run, run si's found by its index
+struct LaunchSlabs {
+  uint64_t fbase, rbase;
+  __device__ explicit LaunchSlabs(const Index& ix) : fbase(ix.ctr[C_RES_FREE]), rbase(ix.ctr[C_RES_RET]) {}
+  __device__ SlabCursor run(uint32_t si) const {
+    SlabCursor cur;
+    if (fbase != ~0ull) {
+      cur.free_hi = fbase - si;
+      cur.free_left = 1;
+    }
+    if (rbase != ~0ull) {
+      cur.ret_next = rbase + si;
+      cur.ret_left = 1;
+    }
+    return cur;
+  }
+};
+
+// with a.slow: the targets k_reverse_cover left, by run index
 template <int G>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k_reverse_chain(Index ix, MaintArgs a) {
   extern __shared__ __align__(16) char smem[];
   if (gated(ix, a.d)) return;
   resolve(ix, a);
+  const ChainLds c = carve_chain(wave_lds(smem, a), ix.R, a.vstride);
+  if (a.slow) {
+    const uint32_t n = (uint32_t)ix.ctr[C_NSLOW];
+    const LaunchSlabs slabs(ix);
+    SlabCursor tally;
+    FOR_EACH_WAVE_ITEM(i, n) {
+      wave_sync();
+      const uint32_t si = a.slow[i];
+      SlabCursor cur = slabs.run(si);
+      reverse_chain_u8<G>(ix, a, c, a.seg[si], cur);
+      return_slabs(ix, cur);
+      tally.pubs += cur.pubs;
+    }
+    finish_slabs_block(ix, tally, C_PUB_REVERSE);
+    return;
+  }
   const uint32_t nseg = (uint32_t)ix.ctr[C_NSEG];
   SlabCursor cur = reserve_slabs_block(ix, wave_items(nseg), wave_items(nseg));
-  const ChainLds c = carve_chain(wave_lds(smem, a), ix.R, a.vstride);
   FOR_EACH_WAVE_ITEM(si, nseg) {
     wave_sync();
     reverse_chain_u8<G>(ix, a, c, a.seg[si], cur);
@@ -2925,7 +2964,8 @@ __global__ void k_del_classify(Index ix, const uint64_t* sorted, uint32_t n, Dyn
   if (m) wave_atomic_add(&ix.ctr[C_DEL_OK], (unsigned long long)__popcll(m));
 }
 
-// <0,d,s> -> <1,d,s>: the flag is set, degree and slab are kept
+// <0,d,s> -> <1,d,s>: the flag is set (and its copy in the bitmap), degree and
+// slab are kept
 __global__ void k_tombstone(Index ix, const uint32_t* dlist, uint32_t n, Dyn d) {
   if (gated(ix, d)) return;
   n = dyn_count(ix, d, n);
@@ -2938,6 +2978,7 @@ __global__ void k_tombstone(Index ix, const uint32_t* dlist, uint32_t n, Dyn d) 
       const uint64_t prev = atomicCAS(&ix.refs[u], (unsigned long long)r, (unsigned long long)(r | (1ull << 63)));
       if (prev == r) {
         done = true;
+        atomicOr(&ix.delbits[u >> 6], 1ull << (u & 63u));
         break;
       }
       r = prev;
@@ -2961,7 +3002,7 @@ __global__ void k_repair_pairs(Index ix, MaintArgs a) {
   uint64_t key = KEY_NONE;
   if ((uint32_t)l < deg && s != NONE) {
     const uint32_t an = ix.slabs[(size_t)s * 2u * ix.R + (uint32_t)l];
-    if (!ref_del(load_ref(ix, an))) key = pair_key(an, u);
+    if (!del_bit(ix, an)) key = pair_key(an, u);
   }
   a.pairs[(size_t)i * ix.R + (uint32_t)l] = key;
 }
@@ -3067,9 +3108,8 @@ __device__ inline void pool_stage(const Index& ix, const PoolLds& p, const uint3
   const int l = lane_id();
   const int ch = l % G, grp = l / G;
   const uint4 ones = make_uint4(0x01010101u, 0x01010101u, 0x01010101u, 0x01010101u);
-  uint64_t ref = 0;
   const uint32_t my = l < cnt ? slots[l] : 0u;
-  if (l < cnt) ref = load_ref(ix, p.id[my]);
+  const bool del = l < cnt && del_bit(ix, p.id[my]);
   for (int base = 0; base < cnt; base += U * VPP) {
     uint4 v[U];
     int sl[U];
@@ -3093,7 +3133,7 @@ __device__ inline void pool_stage(const Index& ix, const PoolLds& p, const uint3
     }
   }
   wave_sync();
-  if (l < cnt && ref_del(ref)) p.dw[my] |= DW_DEAD;
+  if (del) p.dw[my] |= DW_DEAD;
   wave_sync();
 }
 
@@ -3205,7 +3245,7 @@ __device__ inline void pool_first(const Index& ix, const PoolLds& p, uint32_t n,
   constexpr uint32_t KS = (16u * G + 63u) / 64u;
   const int l = lane_id();
   const uint32_t r = (uint32_t)(l & 15), kc = (uint32_t)(l >> 4) * 16u, rb = (uint32_t)(l >> 4) * 4u;
-  const uint64_t ref = (uint32_t)l < nf ? load_ref(ix, p.id[l]) : 0ull;
+  const bool del = (uint32_t)l < nf && del_bit(ix, p.id[l]);
   v4i32 f[4][KS], fa[KS];
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
@@ -3264,7 +3304,7 @@ __device__ inline void pool_first(const Index& ix, const PoolLds& p, uint32_t n,
     }
   }
   wave_sync();
-  if ((uint32_t)l < nf && ref_del(ref)) p.dw[l] |= DW_DEAD;
+  if (del) p.dw[l] |= DW_DEAD;
   wave_sync();
 }
 
@@ -3384,23 +3424,17 @@ struct RepairHead {
   uint64_t ra, ru;
 };
 
-__device__ inline RepairHead repair_heads(const Index& ix, const MaintArgs& a, uint32_t b0, uint32_t nb) {
+// t: lane k's segment start
+__device__ inline RepairHead repair_heads(const Index& ix, const MaintArgs& a, uint32_t t, uint32_t nb) {
   const uint32_t l = (uint32_t)lane_id();
   RepairHead h{KEY_NONE, KEY_NONE, 0, 0};
   if (l < nb) {
-    const uint32_t t = a.seg[b0 + l];
     h.pair = a.pairs[t];
     h.next = t + 1 < a.npairs ? a.pairs[t + 1] : KEY_NONE;
     h.ra = load_ref(ix, (uint32_t)(h.pair >> 32));
     h.ru = load_ref(ix, (uint32_t)h.pair);
   }
   return h;
-}
-
-// lane k < nb: the batch's k-th segment start
-__device__ inline uint32_t l_seg(const MaintArgs& a, uint32_t b0, uint32_t nb) {
-  const uint32_t l = (uint32_t)lane_id();
-  return l < nb ? a.seg[b0 + l] : 0u;
 }
 
 template <int G>
@@ -3563,19 +3597,18 @@ __global__ void k_reserve_launch(Index ix, Dyn d) {
   }
   ix.ctr[C_RES_FREE] = f;
   ix.ctr[C_RES_RET] = r;
+  ix.ctr[C_NSLOW] = 0;
 }
 
-template <int G>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_repair_pool(Index ix, MaintArgs a) {
-  extern __shared__ __align__(16) char smem[];
-  if (gated(ix, a.d)) return;
-  resolve(ix, a);
-  const uint32_t nseg = (uint32_t)ix.ctr[C_NSEG];
-  const uint64_t fbase = ix.ctr[C_RES_FREE], rbase = ix.ctr[C_RES_RET];
-  constexpr uint32_t BATCH = 4;
-  const uint32_t nbat = (nseg + BATCH - 1) / BATCH;
-  const PoolLds p = carve_pool(wave_lds(smem, a), a.vstride);
-  uint32_t pubs = 0;
+// The queue loop of the repair kernels: batches of up to four of n items to
+// body(b0, nb); the last workgroup out resets the queues for the next launch.
+// A batch shares the reads that lead to its items; with few items each wave
+// takes one.
+__device__ inline uint32_t run_batch(uint32_t n) { return max(1u, min(4u, n / total_waves())); }
+
+template <class Body, class End>
+__device__ inline void repair_queues(const Index& ix, uint32_t n, Body body, End end) {
+  const uint32_t batch = run_batch(n), nbat = (n + batch - 1) / batch;
   for (uint32_t qq = 0; qq < N_RQ; ++qq) {
     const uint32_t q = (blockIdx.x + qq) % N_RQ;
     unsigned long long* queue = &ix.ctr[rq_word(q)];
@@ -3585,31 +3618,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
     for (;;) {
       const uint32_t bi = lo + (uint32_t)wave_atomic_add(queue, 1ull);
       if (bi >= hi) break;
-      const uint32_t b0 = bi * BATCH;
-      const uint32_t nb = min(BATCH, nseg - b0);
-      SlabCursor cur;
-      if (fbase != ~0ull) {
-        cur.free_hi = fbase - b0;
-        cur.free_left = nb;
-      }
-      if (rbase != ~0ull) {
-        cur.ret_next = rbase + b0;
-        cur.ret_left = nb;
-      }
-      const RepairHead hd = repair_heads(ix, a, b0, nb);
-      const uint32_t ts = l_seg(a, b0, nb);
-      for (uint32_t k = 0; k < nb; ++k) {
-        wave_sync();
-        repair_chain_u8<G>(ix, a, p, (uint32_t)__builtin_amdgcn_readlane((int)ts, (int)k), hd, (int)k, cur);
-      }
-      return_slabs(ix, cur);
-      pubs += cur.pubs;
+      body(bi * batch, min(batch, n - bi * batch));
     }
   }
-  SlabCursor tally;
-  tally.pubs = pubs;
-  finish_slabs_block(ix, tally, C_PUB_REPAIR);  // ends with a workgroup barrier
-  // the last workgroup out resets the queues for the next launch
+  end();  // ends with a workgroup barrier
   if (threadIdx.x == 0) {
     const unsigned long long done = atomicAdd(&ix.ctr[C_QDONE], 1ull);
     if (done + 1 == gridDim.x) {
@@ -3617,6 +3629,588 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
       atomicExch(&ix.ctr[C_QDONE], 0ull);
     }
   }
+}
+
+// with a.slow: the targets k_repair_cover left, by run index
+template <int G>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_repair_pool(Index ix, MaintArgs a) {
+  extern __shared__ __align__(16) char smem[];
+  if (gated(ix, a.d)) return;
+  resolve(ix, a);
+  const PoolLds p = carve_pool(wave_lds(smem, a), a.vstride);
+  const LaunchSlabs slabs(ix);
+  SlabCursor tally;
+  repair_queues(
+      ix, (uint32_t)ix.ctr[a.slow ? C_NSLOW : C_NSEG],
+      [&](uint32_t b0, uint32_t nb) {
+        const uint32_t l = (uint32_t)lane_id();
+        const uint32_t si = l < nb ? (a.slow ? a.slow[b0 + l] : b0 + l) : 0u;
+        const uint32_t ts = l < nb ? a.seg[si] : 0u;
+        const RepairHead hd = repair_heads(ix, a, ts, nb);
+        for (uint32_t k = 0; k < nb; ++k) {
+          wave_sync();
+          SlabCursor cur = slabs.run((uint32_t)__builtin_amdgcn_readlane((int)si, (int)k));
+          repair_chain_u8<G>(ix, a, p, (uint32_t)__builtin_amdgcn_readlane((int)ts, (int)k), hd, (int)k, cur);
+          return_slabs(ix, cur);
+          tally.pubs += cur.pubs;
+        }
+      },
+      [&] { finish_slabs_block(ix, tally, C_PUB_REPAIR); });
+}
+
+// ---- prunes with few covered pairs (uint8 rows, dim <= 128, R <= 32) -----------------------
+// RobustPrune drops a candidate y only when an earlier kept x covers it: a^2
+// D(x, y) <= b^2 D(p, y). The earlier of two candidates is the nearer one, so
+// the pair's test is a^2 D(x, y) <= b^2 max(D(p, x), D(p, y)), whatever their
+// order, and a prune is known from the few pairs that pass it: without one it
+// keeps the first R in (distance, id) order. In a cluster of many dimensions a
+// node's near neighbors are farther from each other than 1 / alpha of their
+// distance to it, so passing pairs are rare: none in 96% of the reverse-edge
+// prunes and 26% of the repairs at 1M rows, four on average and ten at the 90th
+// percentile in the repairs (64 candidates, 2,016 pairs). These kernels need
+// neither a table of distances in LDS nor the ordered selection over it: the
+// matrix cores give all pairs' products (v_mfma_i32_16x16x64_i8 over the rows
+// shifted to signed bytes, exact as everywhere), each lane tests the pairs it
+// holds of a tile where they are, and the lists are merged by one sort of 64
+// keys in registers. A target with more passing pairs than they take is left,
+// untouched, to the general kernel, through a list of run indices; its reserved
+// slabs stay its own. Bound: vector issue (about 650 instructions per deleted
+// neighbor, two thirds of the SIMD cycles) and the reads that lead to the rows;
+// 4 waves per SIMD (5 spill: 2.87 -> 3.02 ms per pass). 10,000 deletes and
+// 10,000 inserts at 1M rows, with the general kernels' remainder: repair 2.05 ->
+// 0.70 ms, reverse edges 1.14 -> 0.30 (2,000 and 2,000 at 200k: 0.52 -> 0.22,
+// 0.28 -> 0.09).
+struct CoverLds {
+  uint32_t* id;    // [64] the current target's ids by slot (one of bid's rows)
+  uint32_t* an;    // [64] a^2 times the shifted squared norm; COVER_OUT for a slot that takes no part
+  uint32_t* thr;   // [64] b^2 times the distance to the target; 0 for such a slot
+  uint32_t* left;  // [64] run indices not yet on the general kernel's list
+  uint32_t* bid;   // [4][64] ids by slot of a batch of targets
+  uint32_t* bld;   // [4][32] their lists' stored distances
+};
+// Index::cmp29 bounds both products of two real slots by 2^29, and a^2 times a
+// shifted norm by 2^27, so a pair with one or two such slots never passes
+constexpr uint32_t COVER_OUT = 1u << 30;
+constexpr uint32_t COVER_BATCH = 4;
+constexpr uint32_t COVER_LDS = (3 * 64 + COVER_BATCH * 96) * 4;
+
+__device__ inline CoverLds carve_cover(char* smem) {
+  CoverLds c;
+  c.an = reinterpret_cast<uint32_t*>(smem + (size_t)(threadIdx.x >> 6) * COVER_LDS);
+  c.thr = c.an + 64;
+  c.left = c.an + 128;
+  c.bid = c.an + 192;
+  c.bld = c.bid + COVER_BATCH * 64;
+  c.id = c.bid;
+  return c;
+}
+
+// A publication whose compare-and-swap is in flight: the next target's reads
+// go out before its answer is waited for. The lists of a launch belong to one
+// wave each, so the answer is yes; after a no the run goes to the general
+// kernel, its reserved slabs still its own.
+struct PendingPub {
+  bool on = false;
+  uint32_t si = 0;              // the run
+  uint64_t snap = 0;            // the reference word it replaces
+  unsigned long long prev = 0;  // lane 0: the word it found
+
+  // node u's list (id, d), entry l in lane l < n, into the run's fresh slab
+  __device__ void begin(const Index& ix, uint32_t u, uint32_t id, uint32_t d, uint32_t n, uint64_t word, uint32_t run,
+                        uint32_t fresh) {
+    on = true;
+    si = run;
+    snap = word;
+    const uint32_t l = (uint32_t)lane_id(), R = ix.R;
+    uint32_t* w = ix.slabs + (size_t)fresh * 2u * R;
+    if (l < R) {
+      w[l] = l < n ? id : NONE;
+      w[R + l] = l < n ? d : 0u;
+    }
+    if (ix.fence) __threadfence();  // contents before the reference, for concurrent readers
+    if (l == 0)
+      prev = atomicCAS(&ix.refs[u], (unsigned long long)snap,
+                       (unsigned long long)(make_ref(ref_del(snap), n, fresh) | (snap & REF_NORM_MASK)));
+  }
+  // true when the run has to go to the general kernel
+  __device__ bool finish(const Index& ix, const LaunchSlabs& slabs, uint32_t& pubs) {
+    if (!on) return false;
+    on = false;
+    const bool first = lane_id() == 0;
+    if (bcast(first && prev == snap ? 1u : 0u)) {
+      if (first) ix.retired_stack[slabs.rbase + si] = ref_slab(snap);
+      ++pubs;
+      return false;
+    }
+    if (first) atomicAdd(&ix.ctr[C_CAS_FAIL], 1ull);
+    return true;
+  }
+};
+
+// the reserved fresh slabs of a batch's runs (lane k: run si); NONE where the
+// pool could not cover the launch, whose runs are then all the general kernel's
+__device__ inline uint32_t fresh_slabs(const Index& ix, const LaunchSlabs& s, uint32_t si, bool valid) {
+  return valid && s.fbase != ~0ull && s.rbase != ~0ull ? ix.free_stack[s.fbase - si - 1u] : NONE;
+}
+
+// Runs for the general kernel gather in LDS and take their places in its list
+// 64 at a time (an atomic per run on one address would serialize).
+struct LeftRuns {
+  uint32_t n = 0;
+  __device__ void flush(const Index& ix, const MaintArgs& a, const CoverLds& c) {
+    const uint32_t l = (uint32_t)lane_id();
+    if (!n) return;
+    wave_sync();
+    const uint64_t at = wave_atomic_add(&ix.ctr[C_NSLOW], (unsigned long long)n);
+    if (l < n) a.slow[at + l] = c.left[l];
+    n = 0;
+    wave_sync();
+  }
+  __device__ void add(const Index& ix, const MaintArgs& a, const CoverLds& c, uint32_t si) {
+    if (lane_id() == 0) c.left[n] = si;
+    if (++n == 64) flush(ix, a, c);
+  }
+};
+
+// (distance, id, slot) of a candidate as one key: rows of at most 128 bytes
+// have distances below 2^23
+__device__ inline uint64_t slot_key(uint32_t d, uint32_t id, uint32_t slot) {
+  return ((uint64_t)d << 38) | ((uint64_t)id << 6) | slot;
+}
+__device__ inline uint32_t slot_key_dist(uint64_t k) { return (uint32_t)(k >> 38); }
+
+// The rows of T tiles of 16 slots (id NONE: empty) as matrix operands, the
+// target's row, and what the tests need of them.
+template <int G, int T>
+struct CoverTiles {
+  static constexpr uint32_t DIM = 16u * G, KS = (DIM + 63u) / 64u;
+  v4i32 f[T][KS];
+  uint32_t norm;  // lane l: slot l's shifted squared norm (l < 16 T)
+  uint32_t dist;  // lane l: slot l's squared distance to the target
+
+  __device__ void load(const Index& ix, const CoverLds& c, uint32_t target) {
+    const int l = lane_id();
+    const uint32_t r = (uint32_t)(l & 15), k4 = (uint32_t)(l >> 4), kc = k4 * 16u;
+    // a row is 16 G bytes; an empty slot reads the target's row, whose products
+    // are never used
+    auto frag = [&](uint32_t id, uint32_t off) {
+      v4i32 v = {0, 0, 0, 0};
+      if (DIM % 64u == 0 || off < DIM) {
+        const uint4 w = *reinterpret_cast<const uint4*>(ix.x + (size_t)id * DIM + off);
+        v = v4i32{(int)(w.x ^ 0x80808080u), (int)(w.y ^ 0x80808080u), (int)(w.z ^ 0x80808080u),
+                  (int)(w.w ^ 0x80808080u)};
+      }
+      return v;
+    };
+    v4i32 fa[KS];
+#pragma unroll
+    for (int h = 0; h < T; ++h) {
+      uint32_t id = c.id[h * 16 + (int)r];
+      id = id == NONE ? target : id;
+#pragma unroll
+      for (uint32_t ks = 0; ks < KS; ++ks) f[h][ks] = frag(id, ks * 64u + kc);
+    }
+#pragma unroll
+    for (uint32_t ks = 0; ks < KS; ++ks) fa[ks] = frag(target, ks * 64u + kc);
+    v4i32 aa = {0, 0, 0, 0};
+#pragma unroll
+    for (uint32_t ks = 0; ks < KS; ++ks) aa = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[ks], fa[ks], aa, 0, 0, 0);
+    // the target's tile: every row is the target, so every lane holds column l % 16
+    int dt = 0;
+    v4i32 diag[T];
+#pragma unroll
+    for (int h = 0; h < T; ++h) {
+      v4i32 t = {0, 0, 0, 0};
+      diag[h] = v4i32{0, 0, 0, 0};
+#pragma unroll
+      for (uint32_t ks = 0; ks < KS; ++ks) {
+        diag[h] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[h][ks], f[h][ks], diag[h], 0, 0, 0);
+        t = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[ks], f[h][ks], t, 0, 0, 0);
+      }
+      if (k4 == (uint32_t)h) dt = t[0];
+    }
+    // the norms lie on the diagonals: lane (l % 16, l / 16) holds rows 4 (l / 16) + i
+    if ((r >> 2) == k4) {
+#pragma unroll
+      for (int h = 0; h < T; ++h)
+        c.an[h * 16 + (int)r] = (uint32_t)((r & 2u) ? (r & 1u) ? diag[h][3] : diag[h][2]
+                                                    : (r & 1u) ? diag[h][1] : diag[h][0]);
+    }
+    wave_sync();
+    norm = l < 16 * T ? c.an[l] : 0u;
+    dist = (uint32_t)aa[0] + norm - 2u * (uint32_t)dt;
+    wave_sync();
+  }
+
+  // The pairs of slots that take part (in; lane l: slot l, at distance d to
+  // the target) and pass the cover test. hit: four bits per tile pair (g, h), in
+  // the order g, then h from g up: pair (16 g + 4 (l / 16) + i, 16 h + l % 16)
+  // passes when bit i of them is set in lane l. Tile pairs without one (most)
+  // cost four tests and one scalar branch. Returns whether any passes.
+  __device__ bool covers(const Index& ix, const CoverLds& c, bool in, uint32_t d, uint64_t& hit) {
+    const int l = lane_id();
+    const uint32_t r = (uint32_t)(l & 15), rb = (uint32_t)(l >> 4) * 4u;
+    c.an[l] = in ? __umul24(ix.a2, norm) : COVER_OUT;
+    c.thr[l] = in ? __umul24(ix.b2, d) : 0u;
+    wave_sync();
+    const int c2 = -2 * (int)ix.a2;
+    uint32_t ac[T], tc[T];
+#pragma unroll
+    for (int h = 0; h < T; ++h) {
+      ac[h] = c.an[h * 16 + (int)r];
+      tc[h] = c.thr[h * 16 + (int)r];
+    }
+    hit = 0;
+    uint64_t any = 0;
+    int at = 0;
+#pragma unroll
+    for (int g = 0; g < T; ++g) {
+      const uint4 av = *reinterpret_cast<const uint4*>(c.an + g * 16 + (int)rb);
+      const uint4 tv = *reinterpret_cast<const uint4*>(c.thr + g * 16 + (int)rb);
+      const uint32_t ar[4] = {av.x, av.y, av.z, av.w}, tr[4] = {tv.x, tv.y, tv.z, tv.w};
+#pragma unroll
+      for (int h = g; h < T; ++h, at += 4) {
+        v4i32 acc = {0, 0, 0, 0};
+#pragma unroll
+        for (uint32_t ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[g][ks], f[h][ks], acc, 0, 0, 0);
+        bool p[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)  // a^2 D(row, column) against the larger threshold
+          p[i] = ar[i] + ac[h] + (uint32_t)__mul24(c2, acc[i]) <= max(tr[i], tc[h]) && (h > g || rb + (uint32_t)i < r);
+        const uint64_t m = ballot(p[0]) | ballot(p[1]) | ballot(p[2]) | ballot(p[3]);
+        if (m) {
+          any |= m;
+          hit |= (uint64_t)((p[0] ? 1u : 0u) | (p[1] ? 2u : 0u) | (p[2] ? 4u : 0u) | (p[3] ? 8u : 0u)) << at;
+        }
+      }
+    }
+    wave_sync();
+    return any != 0;
+  }
+
+  // the pairs of a hit word, one by one (rows and columns uniform)
+  template <class Pair>
+  __device__ static void each(uint64_t hit, Pair pair) {
+    // tile pair k's g and h, a nibble each
+    constexpr uint64_t G_OF = T == 4 ? 0x3221110000ull : 0x211000ull, H_OF = T == 4 ? 0x3323213210ull : 0x221210ull;
+    for (uint64_t lanes = ballot(hit != 0); lanes; lanes &= lanes - 1ull) {
+      const uint32_t e = (uint32_t)__builtin_ctzll(lanes);
+      for (uint64_t w = bcast_lane64(hit, (int)e); w; w &= w - 1ull) {
+        const uint32_t b = (uint32_t)__builtin_ctzll(w), sh = b & ~3u;
+        pair(((uint32_t)(G_OF >> sh) & 15u) * 16u + (e >> 4) * 4u + (b & 3u), ((uint32_t)(H_OF >> sh) & 15u) * 16u + (e & 15u));
+      }
+    }
+  }
+};
+
+// Repair of one target (Algorithm 3): for each deleted u, K = RobustPrune(a,
+// N(u) \ {a}), then the list becomes RobustPrune(a, (N(a) \ {u}) U K), both
+// from the passing pairs alone. Slots 0..31 hold the list, 32..63 N(u); a member
+// of N(u) that is listed takes part in K's prune through its list slot. Returns
+// false, with nothing changed, at a pair (a, u) with more than COVER_MAX.
+constexpr uint32_t COVER_MAX = 512, COVER_DROPS = 8;
+
+template <int G>
+__device__ inline bool repair_cover_u8(const Index& ix, const MaintArgs& a, const CoverLds& c, uint32_t t,
+                                       const RepairHead& hd, int k, uint32_t& n, uint32_t& lid, uint32_t& ld) {
+  const uint32_t l = (uint32_t)lane_id();
+  const uint32_t R = ix.R;
+  const uint32_t an = (uint32_t)(bcast_lane64(hd.pair, k) >> 32);
+  const uint64_t ra = bcast_lane64(hd.ra, k), pair1 = bcast_lane64(hd.next, k);
+  n = ref_slab(ra) == NONE ? 0u : ref_deg(ra);
+  // the list in (distance, id) order, entry l in lane l < n
+  lid = NONE;
+  ld = l < 32u ? c.bld[k * 32 + (int)l] : 0u;
+  for (uint32_t q = t; q < a.npairs; ++q) {
+    if (q != t) {
+      const uint64_t pq = q == t + 1 ? pair1 : a.pairs[q];
+      if (pq == KEY_NONE || (uint32_t)(pq >> 32) != an) break;
+      const uint64_t ru = bcast64(load_ref(ix, (uint32_t)pq));
+      const uint32_t du = ref_slab(ru) == NONE ? 0u : ref_deg(ru);
+      uint32_t x = l < n ? lid : NONE;
+      if (l >= 32u && l - 32u < du) {
+        x = ix.slabs[(size_t)ref_slab(ru) * 2u * R + (l - 32u)];
+        if (x == an) x = NONE;
+      }
+      wave_sync();
+      c.id[l] = x;
+      wave_sync();
+    }
+    const uint32_t id = c.id[l];
+    const bool live = id != NONE && !del_bit(ix, id);  // u itself carries the flag
+    CoverTiles<G, 4> tiles;
+    tiles.load(ix, c, an);
+    const uint32_t d = l < 32u ? ld : tiles.dist;
+    // live slots by rank, distance and slot in one word: an id that is both
+    // listed and in N(u) comes out as two neighbors of one distance. Two ids of
+    // one distance (their order is the id's) take a sort of 64-bit keys.
+    uint32_t rk = live ? (d << 6) | l : NONE;
+    wave_sort32(rk);
+    uint32_t rid = c.id[rk & 63u], pid = lane_shr1(rid), pk = lane_shr1(rk);
+    bool same = rk != NONE && l > 0 && (pk >> 6) == (rk >> 6);
+    if (ballot(same && rid != pid)) {
+      uint64_t key[1] = {live ? slot_key(d, id, l) : KEY_NONE};
+      wave_sort_regs<1>(key);
+      rk = key[0] == KEY_NONE ? NONE : (slot_key_dist(key[0]) << 6) | ((uint32_t)key[0] & 63u);
+      rid = c.id[rk & 63u];
+      pid = lane_shr1(rid);
+      pk = lane_shr1(rk);
+      same = rk != NONE && l > 0 && rid == pid;
+    }
+    const uint32_t slot = rk & 63u;
+    // each slot's part, through LDS: bit 31 a live one, bit 30 in N(u) (a
+    // listed id through its list slot), and the rank
+    const uint64_t dups = ballot(same);
+    const uint64_t ranked = ballot(rk != NONE) & ~dups;
+    c.an[l] = 0;
+    wave_sync();
+    if (rk != NONE && !same)
+      c.an[slot] = 0x80000000u | (slot >= 32u || ((dups >> 1) >> l) & 1ull ? 0x40000000u : 0u) | lanes_below(ranked);
+    wave_sync();
+    const uint32_t part = c.an[l];
+    wave_sync();
+    const bool in = part >> 31;
+    const uint64_t mb = ballot((part >> 30) == 3u);  // N(u)'s live members, by slot
+    uint64_t kept = ranked;
+    // At most COVER_DROPS drops leave the R kept ones among the first R +
+    // COVER_DROPS, so only those pairs matter; more drops than that, and all do
+    for (uint32_t within = R + COVER_DROPS;; within = 64u) {
+      // lane l: the slots whose pair with slot l passes
+      uint64_t cov = 0, hit;
+      if (!tiles.covers(ix, c, in && (part & 63u) < within, d, hit)) break;
+      if (bcast(group_sum<64>((uint32_t)__popcll(hit))) > COVER_MAX) return false;
+      CoverTiles<G, 4>::each(hit, [&](uint32_t row, uint32_t col) {
+        if (l == row) cov |= 1ull << col;
+        if (l == col) cov |= 1ull << row;
+      });
+      // the members of `set` (by slot) that an earlier kept one covers, over the
+      // members of rank mask `rm` in order
+      auto dropped = [&](uint64_t set, uint64_t rm) {
+        uint64_t out = 0;
+        for (; rm; rm &= rm - 1ull) {
+          const int s = __builtin_amdgcn_readlane((int)slot, (int)__builtin_ctzll(rm));
+          if ((out >> s) & 1ull) continue;
+          out |= bcast_lane64(cov, s) & set;
+        }
+        return out;
+      };
+      uint64_t uni = ballot(in);
+      const uint64_t ib = ballot((cov & mb) != 0) & mb;  // N(u)'s members with a passing pair among them
+      if (ib) uni &= ~(dropped(mb, ranked & ballot((ib >> slot) & 1ull)) & 0xFFFFFFFF00000000ull);
+      // the list (its entries stay, in K or not) with K, at most prune_cap of them
+      kept = ranked & ballot((uni >> slot) & 1ull);
+      if ((uint32_t)__popcll(kept) > ix.prune_cap) {
+        uint64_t rest = kept;
+        for (uint32_t j = 0; j < ix.prune_cap; ++j) rest &= rest - 1ull;
+        kept &= ~rest;
+      }
+      const uint64_t iu = ballot((cov & uni) != 0) & uni;
+      if (iu) {
+        const uint64_t out = dropped(uni, kept & ballot((iu >> slot) & 1ull));
+        kept &= ~ballot((out >> slot) & 1ull);
+      }
+      if (within == 64u || (uint32_t)__popcll(ranked & ~kept) <= COVER_DROPS) break;
+    }
+    n = min(R, (uint32_t)__popcll(kept));
+    lid = rid;
+    ld = rk >> 6;
+    if (kept & (kept + 1ull)) {  // gaps: the kept ones move up (the others to the lanes past them)
+      const uint32_t kc = (uint32_t)__popcll(kept), below = lanes_below(kept);
+      const uint32_t to = 4u * (((kept >> l) & 1ull) ? below : kc + l - below);
+      lid = (uint32_t)__builtin_amdgcn_ds_permute((int)to, (int)lid);
+      ld = (uint32_t)__builtin_amdgcn_ds_permute((int)to, (int)ld);
+    }
+  }
+  return true;
+}
+
+template <int G>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_repair_cover(Index ix, MaintArgs a) {
+  __shared__ __align__(16) char smem[4 * COVER_LDS];
+  if (gated(ix, a.d)) return;
+  resolve(ix, a);
+  CoverLds c = carve_cover(smem);
+  const LaunchSlabs slabs(ix);
+  SlabCursor tally;
+  LeftRuns left;
+  PendingPub pend;
+  repair_queues(
+      ix, (uint32_t)ix.ctr[C_NSEG],
+      [&](uint32_t b0, uint32_t nb) {
+        const uint32_t l = (uint32_t)lane_id();
+        const uint32_t ts = l < nb ? a.seg[b0 + l] : 0u;
+        const uint32_t fresh = fresh_slabs(ix, slabs, b0 + l, l < nb);
+        const RepairHead hd = repair_heads(ix, a, ts, nb);
+        // the batch's lists and first N(u)s, all in flight together
+        uint32_t bi[COVER_BATCH], bd[COVER_BATCH];
+#pragma unroll
+        for (uint32_t k = 0; k < COVER_BATCH; ++k) {
+          const uint64_t r = l < 32u ? bcast_lane64(hd.ra, (int)k) : bcast_lane64(hd.ru, (int)k);
+          const uint32_t deg = k < nb && ref_slab(r) != NONE ? ref_deg(r) : 0u;
+          const uint32_t* w = ix.slabs + (size_t)ref_slab(r) * 2u * ix.R + (l & 31u);
+          bi[k] = NONE;
+          bd[k] = 0;
+          if ((l & 31u) < deg) {
+            bi[k] = w[0];
+            if (l < 32u) bd[k] = w[ix.R];
+          }
+        }
+        wave_sync();
+#pragma unroll
+        for (uint32_t k = 0; k < COVER_BATCH; ++k) {
+          const uint32_t an = (uint32_t)(bcast_lane64(hd.pair, (int)k) >> 32);
+          c.bid[k * 64u + l] = bi[k] == an ? NONE : bi[k];  // N(u) without a
+          if (l < 32u) c.bld[k * 32u + l] = bd[k];
+        }
+        wave_sync();
+        for (uint32_t k = 0; k < nb; ++k) {
+          c.id = c.bid + k * 64u;
+          const uint64_t ra = bcast_lane64(hd.ra, (int)k);
+          const uint32_t slab = (uint32_t)__builtin_amdgcn_readlane((int)fresh, (int)k);
+          uint32_t n, lid, ld;
+          const bool done = slab != NONE && ref_slab(ra) != NONE &&
+                            repair_cover_u8<G>(ix, a, c, (uint32_t)__builtin_amdgcn_readlane((int)ts, (int)k), hd, (int)k, n,
+                                               lid, ld);
+          if (pend.finish(ix, slabs, tally.pubs)) left.add(ix, a, c, pend.si);
+          if (done)
+            pend.begin(ix, (uint32_t)(bcast_lane64(hd.pair, (int)k) >> 32), lid, ld, n, ra, b0 + k, slab);
+          else
+            left.add(ix, a, c, b0 + k);
+        }
+      },
+      [&] {
+        if (pend.finish(ix, slabs, tally.pubs)) left.add(ix, a, c, pend.si);
+        left.flush(ix, a, c);
+        finish_slabs_block(ix, tally, C_PUB_REPAIR);
+      });
+}
+
+// Reverse edges of one target while no pair among its live list entries and its
+// offers (at most 15) is covered: an offer then enters in (distance, id) order,
+// and at R entries the prune drops the flagged ones and the last. Slots 0..31
+// hold the list (n entries), 32.. the m offers in ascending order. Returns
+// false, with nothing changed, where the general kernel has to decide.
+template <int G>
+__device__ inline bool reverse_cover_u8(const Index& ix, const CoverLds& c, uint32_t w, uint32_t m, uint32_t ld,
+                                        uint32_t& n, uint64_t& key) {
+  const uint32_t l = (uint32_t)lane_id();
+  const uint32_t R = ix.R;
+  const uint32_t id = c.id[l];
+  bool dead = l < n && del_bit(ix, id);
+  CoverTiles<G, 3> tiles;
+  tiles.load(ix, c, w);
+  const uint32_t d = l < 32u ? ld : tiles.dist;
+  if (n + m > R) {  // else nothing is pruned
+    // an offer that is listed (a bootstrap's) takes part through its list slot
+    uint32_t x = ~0u;
+    for (uint32_t k4 = 0; k4 < 32u; k4 += 4) {
+      const uint4 v = *reinterpret_cast<const uint4*>(c.id + k4);
+      x = min(min(x, min(v.x ^ id, v.y ^ id)), min(v.z ^ id, v.w ^ id));
+    }
+    const bool in = id != NONE && !dead && (l < 32u || x != 0u);
+    uint64_t hit;
+    if (tiles.covers(ix, c, in, d, hit)) return false;
+  }
+  const uint64_t offer = make_key(d, id);  // lanes 32 .. 32 + m - 1
+  key = l < n ? offer : KEY_NONE;
+  for (uint32_t j = 0; j < m; ++j) {
+    const uint64_t kv = bcast_lane64(offer, (int)(32u + j));
+    if (ballot(l < n && key_id(key) == key_id(kv))) continue;  // a set union
+    if (n == R) {  // the prune drops the flagged entries
+      const uint64_t dm = ballot(l < n && dead);
+      if (dm) {
+        const uint32_t gone = (uint32_t)__popcll(dm), stay = n - gone;
+        // live entries move up; the rest of the lanes take the places past them
+        const uint32_t to = l < n ? (dead ? stay + lanes_below(dm) : l - lanes_below(dm)) : l;
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_permute((int)(to * 4u), (int)(uint32_t)key);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_permute((int)(to * 4u), (int)(uint32_t)(key >> 32));
+        n = stay;
+        key = l < n ? ((uint64_t)hi << 32) | lo : KEY_NONE;
+        dead = false;
+      }
+    }
+    const uint32_t pos = (uint32_t)__popcll(ballot(key < kv));  // lanes past n hold KEY_NONE
+    const uint64_t up = lane_shr1_64(key);
+    const uint32_t dup = lane_shr1(dead ? 1u : 0u);
+    if (l > pos) {
+      key = up;
+      dead = dup != 0;
+    } else if (l == pos) {
+      key = kv;
+      dead = false;
+    }
+    n = min(R, n + 1u);
+    if (l >= n) key = KEY_NONE;
+  }
+  return true;
+}
+
+// Waves take batches of four runs (static stride: targets cost about the same),
+// whose pairs (lanes 16k .. 16k + 15: run k's first sixteen), reference words
+// and lists are read together.
+template <int G>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_reverse_cover(Index ix, MaintArgs a) {
+  __shared__ __align__(16) char smem[4 * COVER_LDS];
+  if (gated(ix, a.d)) return;
+  resolve(ix, a);
+  CoverLds c = carve_cover(smem);
+  const uint32_t l = (uint32_t)lane_id(), g = l >> 4, j = l & 15u;
+  const uint32_t nseg = (uint32_t)ix.ctr[C_NSEG];
+  const LaunchSlabs slabs(ix);
+  SlabCursor tally;
+  LeftRuns left;
+  PendingPub pend;
+  const uint32_t batch = run_batch(nseg);
+  FOR_EACH_WAVE_ITEM(bi, (nseg + batch - 1) / batch) {
+    const uint32_t b0 = bi * batch, nb = min(batch, nseg - b0);
+    const uint32_t fresh = fresh_slabs(ix, slabs, b0 + l, l < nb);
+    const uint32_t t = g < nb ? a.seg[b0 + g] : 0u;
+    const uint64_t pr = g < nb && t + j < a.npairs ? a.pairs[t + j] : KEY_NONE;
+    const uint32_t w = (uint32_t)__shfl((int)(uint32_t)(pr >> 32), (int)(l & 48u), 64);
+    const uint64_t mine = ballot(pr != KEY_NONE && (uint32_t)(pr >> 32) == w);
+    const uint64_t rw = g < nb ? load_ref(ix, w) : REF_UNBORN;
+    uint32_t bl[COVER_BATCH], bd[COVER_BATCH];
+#pragma unroll
+    for (uint32_t k = 0; k < COVER_BATCH; ++k) {
+      const uint64_t r = bcast_lane64(rw, (int)(16u * k));
+      const uint32_t deg = ref_slab(r) != NONE ? ref_deg(r) : 0u;
+      const uint32_t* s = ix.slabs + (size_t)ref_slab(r) * 2u * ix.R + l;
+      bl[k] = NONE;
+      bd[k] = 0;
+      if (l < deg) {
+        bl[k] = s[0];
+        bd[k] = s[ix.R];
+      }
+    }
+    wave_sync();
+#pragma unroll
+    for (uint32_t k = 0; k < COVER_BATCH; ++k) {
+      c.bid[k * 64u + l] = bl[k];
+      if (l < 32u) c.bld[k * 32u + l] = bd[k];
+    }
+    wave_sync();
+    if (j < (uint32_t)__builtin_ctz(~(uint32_t)(mine >> (16u * g)) | 0x10000u)) c.bid[g * 64u + 32u + j] = (uint32_t)pr;
+    wave_sync();
+    for (uint32_t k = 0; k < nb; ++k) {
+      const uint32_t m = (uint32_t)__builtin_ctz(~(uint32_t)(mine >> (16u * k)) | 0x10000u);  // its offers (16: or more)
+      const uint64_t r = bcast_lane64(rw, (int)(16u * k));
+      const uint32_t wk = (uint32_t)__builtin_amdgcn_readlane((int)w, (int)(16u * k));
+      c.id = c.bid + k * 64u;
+      uint32_t n = ref_slab(r) != NONE ? ref_deg(r) : 0u;
+      const uint32_t slab = (uint32_t)__builtin_amdgcn_readlane((int)fresh, (int)k);
+      uint64_t key;
+      const bool done = slab != NONE && ref_slab(r) != NONE && m < 16u &&
+                        reverse_cover_u8<G>(ix, c, wk, m, l < 32u ? c.bld[k * 32u + l] : 0u, n, key);
+      if (pend.finish(ix, slabs, tally.pubs)) left.add(ix, a, c, pend.si);
+      if (done)
+        pend.begin(ix, wk, key_id(key), key_dist(key), n, r, b0 + k, slab);
+      else
+        left.add(ix, a, c, b0 + k);
+    }
+  }
+  if (pend.finish(ix, slabs, tally.pubs)) left.add(ix, a, c, pend.si);
+  left.flush(ix, a, c);
+  finish_slabs_block(ix, tally, C_PUB_REVERSE);
 }
 
 // ---- stable LSD radix sort with a launch-time count --------------------------------------
@@ -3727,27 +4321,11 @@ __global__ void __launch_bounds__(256) k_rs_scatter(Index ix, const uint64_t* in
 }
 
 // ---- reclaim (Algorithm 4) -------------------------------------------------------------
-__global__ void k_del_bitmap(Index ix, uint64_t n_ids, Dyn d, uint64_t* bitmap) {
-  if (gated(ix, d)) return;
-  n_ids = dyn_count(ix, d, (uint32_t)n_ids);
-  const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t == 0) {
-    ix.ctr[C_DIRTY] = 0;
-    ix.ctr[C_DEAD] = 0;
-  }
-  const bool flagged = t < n_ids && ref_del(load_ref(ix, (uint32_t)t));
-  const uint64_t m = ballot(flagged);
-  if (lane_id() == 0 && t < n_ids) bitmap[t >> 6] = m;
-}
-
-__device__ inline bool bit_set(const uint64_t* bm, uint32_t id) { return (bm[id >> 6] >> (id & 63u)) & 1ull; }
-
 // live nodes with an edge into a tombstone ("dirty"), and the count of such
 // edges; neighbors are tested against the deletion bitmap.
 constexpr uint32_t DIRTY_CHUNK = 1024;  // nodes per workgroup and step
 
-__global__ void __launch_bounds__(256) k_dirty(Index ix, uint64_t n_ids, Dyn d, const uint64_t* bitmap,
-                                               uint32_t* dirty) {
+__global__ void __launch_bounds__(256) k_dirty(Index ix, uint64_t n_ids, Dyn d, uint32_t* dirty) {
   __shared__ uint32_t buf[DIRTY_CHUNK];
   __shared__ uint32_t cnt_s, dead_s, base_s;
   if (gated(ix, d)) return;
@@ -3793,10 +4371,10 @@ __global__ void __launch_bounds__(256) k_dirty(Index ix, uint64_t n_ids, Dyn d, 
         for (uint32_t k = 0; k < 8; ++k) {
           const uint32_t j = 4u * c;
           uint32_t cn = 0;
-          if (j < dg[k]) cn += bit_set(bitmap, w[k].x);
-          if (j + 1 < dg[k]) cn += bit_set(bitmap, w[k].y);
-          if (j + 2 < dg[k]) cn += bit_set(bitmap, w[k].z);
-          if (j + 3 < dg[k]) cn += bit_set(bitmap, w[k].w);
+          if (j < dg[k]) cn += del_bit(ix, w[k].x);
+          if (j + 1 < dg[k]) cn += del_bit(ix, w[k].y);
+          if (j + 2 < dg[k]) cn += del_bit(ix, w[k].z);
+          if (j + 3 < dg[k]) cn += del_bit(ix, w[k].w);
           cn = group_sum<8>(cn);
           const uint32_t got = (uint32_t)__shfl((int)cn, (int)((l & 7) * 8), 64);
           if ((uint32_t)(l >> 3) == k) dead = got;
@@ -3814,13 +4392,13 @@ __global__ void __launch_bounds__(256) k_dirty(Index ix, uint64_t n_ids, Dyn d, 
             if ((R & 3u) == 0) {
               for (uint32_t j = 4u * c; j < deg; j += 32u) {
                 const uint4 w = *reinterpret_cast<const uint4*>(ids + j);
-                cn += bit_set(bitmap, w.x);
-                if (j + 1 < deg) cn += bit_set(bitmap, w.y);
-                if (j + 2 < deg) cn += bit_set(bitmap, w.z);
-                if (j + 3 < deg) cn += bit_set(bitmap, w.w);
+                cn += del_bit(ix, w.x);
+                if (j + 1 < deg) cn += del_bit(ix, w.y);
+                if (j + 2 < deg) cn += del_bit(ix, w.z);
+                if (j + 3 < deg) cn += del_bit(ix, w.w);
               }
             } else {
-              for (uint32_t j = c; j < deg; j += 8u) cn += bit_set(bitmap, ids[j]);
+              for (uint32_t j = c; j < deg; j += 8u) cn += del_bit(ix, ids[j]);
             }
           }
         }
@@ -3870,7 +4448,7 @@ __device__ inline void compact_read(const Index& ix, uint64_t r, uint32_t& id, u
 // the publication starts from the word already read (no other wave touches
 // a dirty node in this phase).
 __global__ void __launch_bounds__(256) k_compact(Index ix, const uint32_t* dirty, uint64_t n, Dyn dn,
-                                                 const uint64_t* bitmap, uint32_t lds_per_wave) {
+                                                 uint32_t lds_per_wave) {
   extern __shared__ __align__(16) char smem[];
   if (gated(ix, dn)) return;
   const uint32_t cnt = dyn_count(ix, dn, (uint32_t)n);
@@ -3891,7 +4469,7 @@ __global__ void __launch_bounds__(256) k_compact(Index ix, const uint32_t* dirty
       const uint64_t r = bcast_lane64(rl, (int)k);
       uint32_t nid = NONE, ndd = 0;
       if (k + 1 < nb) compact_read(ix, bcast_lane64(rl, (int)k + 1), nid, ndd);
-      const bool keep = id != NONE && !bit_set(bitmap, id);
+      const bool keep = id != NONE && !del_bit(ix, id);
       const uint64_t m = ballot(keep);
       wave_sync();
       if (keep) {
@@ -4265,14 +4843,16 @@ hipError_t launch_recycle(const Index& ix, hipStream_t s) {
 }
 
 hipError_t launch_round_begin(const Index& ix, const uint32_t* counts, uint32_t nd, uint32_t ni, uint32_t nq,
-                              uint32_t max_d, uint32_t max_i, uint32_t max_q, int32_t* status, hipStream_t s) {
-  hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(64), 0, s, ix, counts, nd, ni, nq, max_d, max_i, max_q, status);
+                              uint32_t max_d, uint32_t max_i, uint32_t max_q, int32_t* status, hipStream_t s,
+                              bool reclaim) {
+  hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(64), 0, s, ix, counts, nd, ni, nq, max_d, max_i, max_q, status,
+                     reclaim ? 1u : 0u);
   return hipGetLastError();
 }
 
 hipError_t launch_round_gate(const Index& ix, uint32_t tombstone_only, uint32_t boot_max, int32_t* status,
-                             hipStream_t s) {
-  hipLaunchKernelGGL(k_round_gate, dim3(1), dim3(64), 0, s, ix, tombstone_only, boot_max, status);
+                             hipStream_t s, bool reclaim) {
+  hipLaunchKernelGGL(k_round_gate, dim3(1), dim3(64), 0, s, ix, tombstone_only, boot_max, status, reclaim ? 1u : 0u);
   return hipGetLastError();
 }
 
@@ -4615,6 +5195,14 @@ static void launch_maint_p(MaintKernel which, const Index& ix, const MaintArgs& 
     case MK_REVERSE:
       if constexpr (P::CHAIN) {
         if (a.chain) {
+          if constexpr (P::GL <= 8) {
+            if (a.slow) {
+              hipLaunchKernelGGL(k_reserve_launch, dim3(1), dim3(64), 0, s, ix, a.d);
+              const dim3 b4(256);
+              const unsigned g4 = persist_grid(a.npairs, 4);
+              hipLaunchKernelGGL(k_reverse_cover<P::GL>, resident_grid(k_reverse_cover<P::GL>, g4, b4, 0, sh), b4, 0, s, ix, a);
+            }
+          }
           hipLaunchKernelGGL(k_reverse_chain<P::GL>, resident_grid(k_reverse_chain<P::GL>, grid, blk, lds, sh), blk, lds,
                              s, ix, a);
           break;
@@ -4633,6 +5221,13 @@ static void launch_maint_p(MaintKernel which, const Index& ix, const MaintArgs& 
       if constexpr (P::CHAIN) {
         if (a.chain) {
           hipLaunchKernelGGL(k_reserve_launch, dim3(1), dim3(64), 0, s, ix, a.d);
+          if constexpr (P::GL <= 8) {
+            if (a.slow) {
+              const dim3 b4(256);
+              const unsigned g4 = persist_grid(a.npairs, 4);
+              hipLaunchKernelGGL(k_repair_cover<P::GL>, resident_grid(k_repair_cover<P::GL>, g4, b4, 0, sh), b4, 0, s, ix, a);
+            }
+          }
           hipLaunchKernelGGL(k_repair_pool<P::GL>, resident_grid(k_repair_pool<P::GL>, grid, blk, lds, sh), blk, lds, s,
                              ix, a);
           break;
@@ -4739,27 +5334,18 @@ hipError_t launch_tombstone(const Index& ix, const uint32_t* dlist, uint32_t n, 
   return hipGetLastError();
 }
 
-hipError_t launch_del_bitmap(const Index& ix, uint64_t n_ids, Dyn d, uint64_t* bitmap, hipStream_t s) {
-  if (n_ids == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_del_bitmap, dim3(blocks_for(n_ids, 256)), dim3(256), 0, s, ix, n_ids, d, bitmap);
-  return hipGetLastError();
-}
-
-hipError_t launch_dirty(const Index& ix, uint64_t n_ids, Dyn d, const uint64_t* bitmap, uint32_t* dirty,
-                        hipStream_t s) {
+hipError_t launch_dirty(const Index& ix, uint64_t n_ids, Dyn d, uint32_t* dirty, hipStream_t s) {
   if (n_ids == 0) return hipSuccess;
   const unsigned blocks = blocks_for(n_ids, DIRTY_CHUNK);
   hipLaunchKernelGGL(k_dirty, dim3(blocks < 4 * PERSIST_BLOCKS ? blocks : 4 * PERSIST_BLOCKS), dim3(256), 0, s, ix,
-                     n_ids, d, bitmap, dirty);
+                     n_ids, d, dirty);
   return hipGetLastError();
 }
 
-hipError_t launch_compact(const Index& ix, const uint32_t* dirty, uint64_t n, Dyn d, const uint64_t* bitmap,
-                          hipStream_t s) {
+hipError_t launch_compact(const Index& ix, const uint32_t* dirty, uint64_t n, Dyn d, hipStream_t s) {
   if (n == 0) return hipSuccess;
   const uint32_t per_wave = 512;
-  hipLaunchKernelGGL(k_compact, dim3(persist_grid(n, 4)), dim3(256), 4 * per_wave, s, ix, dirty, n, d, bitmap,
-                     per_wave);
+  hipLaunchKernelGGL(k_compact, dim3(persist_grid(n, 4)), dim3(256), 4 * per_wave, s, ix, dirty, n, d, per_wave);
   return hipGetLastError();
 }
 

@@ -81,6 +81,7 @@ struct MaintArgs {
   uint32_t vstride;        // bytes per staged row
   uint32_t lds_per_wave;
   const uint32_t* seg;     // starts of the runs of one target in the sorted pairs
+  uint32_t* slow = nullptr;  // repair, reverse edges: targets (run indices) left to the general kernel
   uint32_t np_ctr = NO_CTR, np_mult = 1;  // launch-time pair count
   uint32_t chain = 0;      // reverse edges: cached candidate state (uint8 rows, R <= 32)
   uint32_t mx = 0;         // RobustPrune selection on the matrix cores (uint8 rows, dim <= 128, R <= 32)
@@ -93,9 +94,10 @@ hipError_t launch_init(const Index& ix, hipStream_t s);
 hipError_t launch_recycle(const Index& ix, hipStream_t s);
 // round control: counts (device array, or the host values when null), gate
 hipError_t launch_round_begin(const Index& ix, const uint32_t* counts, uint32_t nd, uint32_t ni, uint32_t nq,
-                              uint32_t max_d, uint32_t max_i, uint32_t max_q, int32_t* status, hipStream_t s);
+                              uint32_t max_d, uint32_t max_i, uint32_t max_q, int32_t* status, hipStream_t s,
+                              bool reclaim = false);
 hipError_t launch_round_gate(const Index& ix, uint32_t tombstone_only, uint32_t boot_max, int32_t* status,
-                             hipStream_t s);
+                             hipStream_t s, bool reclaim);
 hipError_t launch_reclaim_gate(const Index& ix, int32_t* status, hipStream_t s);
 hipError_t launch_store_rows(const Index& ix, const void* src, uint32_t* ids_out, uint32_t first, uint32_t n, Dyn d,
                              hipStream_t s);
@@ -130,11 +132,8 @@ hipError_t launch_del_keys(const Index& ix, const uint32_t* ids, uint32_t n, Dyn
 hipError_t launch_del_classify(const Index& ix, const uint64_t* sorted, uint32_t n, Dyn d, uint8_t* status,
                                uint32_t* dlist, hipStream_t s);
 hipError_t launch_tombstone(const Index& ix, const uint32_t* dlist, uint32_t n, Dyn d, hipStream_t s);
-hipError_t launch_del_bitmap(const Index& ix, uint64_t n_ids, Dyn d, uint64_t* bitmap, hipStream_t s);
-hipError_t launch_dirty(const Index& ix, uint64_t n_ids, Dyn d, const uint64_t* bitmap, uint32_t* dirty,
-                        hipStream_t s);
-hipError_t launch_compact(const Index& ix, const uint32_t* dirty, uint64_t n, Dyn d, const uint64_t* bitmap,
-                          hipStream_t s);
+hipError_t launch_dirty(const Index& ix, uint64_t n_ids, Dyn d, uint32_t* dirty, hipStream_t s);
+hipError_t launch_compact(const Index& ix, const uint32_t* dirty, uint64_t n, Dyn d, hipStream_t s);
 hipError_t launch_free_tombstones(const Index& ix, uint64_t n_ids, Dyn d, hipStream_t s);
 hipError_t launch_export(const Index& ix, uint64_t n_ids, uint32_t* nbr, uint32_t* rho, uint8_t* deg, uint8_t* del,
                          uint8_t* has_slab, hipStream_t s);
