@@ -45,10 +45,12 @@ struct etale_index {
   uint32_t* dlist = nullptr;
   uint32_t* dirty = nullptr;
   unsigned long long* bitmap = nullptr;  // deletion flags, one bit per id
-  uint32_t* seg = nullptr;        // run starts of a sorted pair list
-  uint32_t* hist = nullptr;       // radix-sort digit counts
+  uint32_t* seg = nullptr;        // run starts of a grouped pair list
+  uint32_t* rank = nullptr;       // grouping: a pair's arrival rank within its target,
+  uint32_t* tlist = nullptr;      //   and the targets
+  unsigned long long* dmark = nullptr;  // [id_capacity] delete marks
+  uint32_t* tcnt = nullptr;             // [id_capacity] pairs per target while a list is grouped
   int32_t* status = nullptr;      // round status words of the calls that do not take one
-  uint32_t pair_bits = 0;         // bits of an id (the sort range of pair targets)
   bool no_chain = false;          // reverse edges without the cached candidate state
   bool no_mx = false;             // prunes select from staged rows even where the matrix cores could
   uint64_t* scan_keys = nullptr;  // [scan_chunk x 256] initial lists
@@ -477,27 +479,38 @@ etale_status enqueue_reclaim(etale_index* ix, uint64_t n_ids_max, int32_t* statu
   return ETALE_OK;
 }
 
+GroupArgs group_args(const etale_index* ix, uint32_t nmax) {
+  GroupArgs g{};
+  g.raw = ix->pairs_a;
+  g.out = ix->pairs_b;
+  g.rank = ix->rank;
+  g.tlist = ix->tlist;
+  g.seg = ix->seg;
+  g.nmax = nmax;
+  g.d.skip = G_FAIL;
+  g.d.n_mult = ix->cfg.R;
+  return g;
+}
+
 etale_status enqueue_round(etale_index* ix, const RoundPlan& p) {
   const Index& d = ix->dev;
   const uint32_t R = ix->cfg.R;
   hipStream_t s = ix->stream;
   HIP_TRY(launch_round_begin(d, p.counts, p.counts ? 0 : p.max_d, p.counts ? 0 : p.max_i, p.counts ? 0 : p.max_q,
                              p.max_d, p.max_i, p.max_q, p.status, s));
-  // P0: classify the deletes (sorted by id, first occurrence wins), then the gate
+  // P0: classify the deletes (the first occurrence of an id wins), then the gate
   if (p.max_d) {
     Dyn dd;
     dd.skip = G_FAIL;
     dd.n_ctr = C_R_NDEL;
-    HIP_TRY(launch_del_keys(d, p.del_ids, p.max_d, dd, ix->pairs_a, s));
-    uint64_t* sorted = nullptr;
-    HIP_TRY(launch_sort(d, ix->pairs_a, ix->pairs_b, p.max_d, dd, 32, 32, ix->hist, s, &sorted));
-    HIP_TRY(launch_del_classify(d, sorted, p.max_d, dd, p.del_status, ix->dlist, s));
+    HIP_TRY(launch_del_mark(d, p.del_ids, p.max_d, dd, s));
+    HIP_TRY(launch_del_classify(d, p.del_ids, p.max_d, dd, p.del_status, ix->dlist, s));
   }
   HIP_TRY(launch_round_gate(d, ix->cfg.tombstone_only, BOOT_MAX, p.status, s, p.reclaim));
   if (p.max_d) {
     Dyn dt;
     dt.skip = G_FAIL;
-    dt.n_ctr = C_R_NDEL;  // dlist: the sorted deletes, NONE where not accepted
+    dt.n_ctr = C_R_NDEL;  // dlist: the deletes, NONE where not accepted
     HIP_TRY(launch_tombstone(d, ix->dlist, p.max_d, dt, s));
     Dyn dr;
     dr.skip = G_FAIL;
@@ -552,30 +565,25 @@ etale_status enqueue_round(etale_index* ix, const RoundPlan& p) {
     MaintArgs pa = maint_args(ix, 2 * R);
     pa.n = p.max_d;
     pa.dlist = ix->dlist;
-    pa.pairs = ix->pairs_a;
     pa.d.skip = G_FAIL;
     pa.d.n_ctr = C_R_NDEL;
-    HIP_TRY(launch_repair_pairs(d, pa, s));
-    Dyn dp;
-    dp.skip = G_FAIL;
-    dp.n_ctr = C_R_NDEL;
-    dp.n_mult = R;
-    uint64_t* sorted = nullptr;
-    // pairs are written in ascending source order (dlist keeps the sorted
-    // deletes): the target half alone gives (target, source) order
-    HIP_TRY(launch_sort(d, ix->pairs_a, ix->pairs_b, p.max_d * R, dp, 32, (int)ix->pair_bits, ix->hist, s, &sorted));
-    HIP_TRY(launch_segments(d, sorted, p.max_d * R, dp, ix->seg, s));
-    pa.pairs = sorted;
     pa.npairs = p.max_d * R;
     if (ix->cfg.metric == ETALE_METRIC_L2_U8 && R <= 32 && !ix->no_chain &&
         pool_lds_per_wave(pa.vstride) <= 65536u) {
       pa.chain = 1;
       pa.lds_per_wave = pool_lds_per_wave(pa.vstride);  // the pool kernel carves only the pool
-      if (ix->cfg.dim <= 128 && d.cmp29) pa.slow = reinterpret_cast<uint32_t*>(sorted == ix->pairs_a ? ix->pairs_b : ix->pairs_a);
+      if (ix->cfg.dim <= 128 && d.cmp29) pa.slow = reinterpret_cast<uint32_t*>(ix->pairs_a);  // free once grouped
     }
-    pa.np_ctr = C_R_NDEL;
-    pa.np_mult = R;
-    pa.seg = ix->seg;
+    GroupArgs g = group_args(ix, pa.npairs);
+    g.seg_ctr = C_NSEG_REP;
+    g.pair_ctr = C_NPAIR_REP;
+    g.reserve = pa.chain;
+    g.d.n_ctr = C_R_NDEL;
+    HIP_TRY(launch_group_repair(d, pa, g, s));
+    pa.pairs = g.out;
+    pa.seg = g.seg;
+    pa.seg_ctr = g.seg_ctr;
+    pa.np_ctr = g.pair_ctr;
     HIP_TRY(launch_maint(MK_REPAIR, d, pa, pa.npairs, maint_waves_per_block(pa), s));
   }
   // P4: reverse edges in (target, source) order, one publication per target
@@ -585,23 +593,15 @@ etale_status enqueue_round(etale_index* ix, const RoundPlan& p) {
     fa.F = ix->F;
     fa.pairs = ix->pairs_a;
     fa.d = di;
-    HIP_TRY(launch_reverse_pairs(d, fa, s));
     if (ix->concurrent) {
       // concurrent mode: every offer applied on its own, racing by CAS
+      HIP_TRY(launch_reverse_pairs(d, fa, s));
       MaintArgs ra = maint_args(ix, R + 1);
       ra.n = p.max_i;
       ra.pairs = ix->pairs_a;
       ra.d = di;
       HIP_TRY(launch_maint(MK_REVERSE_FAST, d, ra, p.max_i * R, maint_waves_per_block(ra), s));
     } else {
-    Dyn dp;
-    dp.skip = G_FAIL;
-    dp.n_ctr = C_R_NINS;
-    dp.n_mult = R;
-    uint64_t* sorted = nullptr;
-    // pairs are written in ascending source order: the target half alone
-    HIP_TRY(launch_sort(d, ix->pairs_a, ix->pairs_b, p.max_i * R, dp, 32, (int)ix->pair_bits, ix->hist, s, &sorted));
-    HIP_TRY(launch_segments(d, sorted, p.max_i * R, dp, ix->seg, s));
     MaintArgs ra = maint_args(ix, R + 1);
     if (ix->cfg.metric == ETALE_METRIC_L2_U8 && R <= 32 && !ix->no_chain) {
       ra.chain = 1;
@@ -609,15 +609,21 @@ etale_status enqueue_round(etale_index* ix, const RoundPlan& p) {
       // reads rows from memory and stages none
       if (ix->cfg.dim <= 128) ra.vstride = 0;
       ra.lds_per_wave = chain_lds_per_wave(R, ra.vstride);
-      if (ix->cfg.dim <= 128 && d.cmp29) ra.slow = reinterpret_cast<uint32_t*>(sorted == ix->pairs_a ? ix->pairs_b : ix->pairs_a);
+      if (ix->cfg.dim <= 128 && d.cmp29) ra.slow = reinterpret_cast<uint32_t*>(ix->pairs_a);  // free once grouped
     }
     ra.n = p.max_i;
-    ra.pairs = sorted;
     ra.npairs = p.max_i * R;
-    ra.np_ctr = C_R_NINS;
-    ra.np_mult = R;
-    ra.seg = ix->seg;
     ra.d = di;
+    GroupArgs g = group_args(ix, ra.npairs);
+    g.seg_ctr = C_NSEG_REV;
+    g.pair_ctr = C_NPAIR_REV;
+    g.reserve = ra.chain;
+    g.d.n_ctr = C_R_NINS;
+    HIP_TRY(launch_group_reverse(d, fa, g, s));
+    ra.pairs = g.out;
+    ra.seg = g.seg;
+    ra.seg_ctr = g.seg_ctr;
+    ra.np_ctr = g.pair_ctr;
     HIP_TRY(launch_maint(MK_REVERSE, d, ra, ra.npairs, maint_waves_per_block(ra), s));
     }
     // P5: refine (not after a bootstrap)
@@ -755,7 +761,10 @@ etale_status etale_create(const etale_config* cfg, etale_t* out) {
   ALLOC(ix->scan_ncand, (uint64_t)ix->scan_chunk * 64 * 4);
   ALLOC(ix->scan_cand, (uint64_t)ix->scan_chunk * SCAN_KEYS_Q * 8);
   ALLOC(ix->seg, B * R * 4);
-  ALLOC(ix->hist, (uint64_t)sort_hist_words((uint32_t)(B * R)) * 4);
+  ALLOC(ix->rank, B * R * 4);
+  ALLOC(ix->tlist, B * R * 4);
+  ALLOC(ix->dmark, C * 8);
+  ALLOC(ix->tcnt, C * 4);
   ALLOC(ix->status, 16);
 #undef ALLOC
   Index& d = ix->dev;
@@ -792,10 +801,10 @@ etale_status etale_create(const etale_config* cfg, etale_t* out) {
   d.ctr = ix->ctr;
   d.entries = ix->entries;
   d.delbits = ix->bitmap;
+  d.dmark = ix->dmark;
+  d.tcnt = ix->tcnt;
   d.ent_x = ix->ent_x;
   d.ent_norm = ix->ent_norm;
-  ix->pair_bits = 1;
-  while ((1ull << ix->pair_bits) <= C) ++ix->pair_bits;  // every id < 2^bits - 1: a KEY_NONE target sorts last
   if (launch_init(d, ix->stream) != hipSuccess || hipStreamSynchronize(ix->stream) != hipSuccess)
     return cleanup(ETALE_EDEVICE, "init");
   if (noalloc_scratch_address(&ix->noalloc) != hipSuccess) return cleanup(ETALE_EDEVICE, "scratch symbol");

@@ -69,13 +69,17 @@ enum Counter {
   C_R_NQ,
   C_R_FIRST,   // this round's first new id
   C_R_GATE,    // GateBits of this round
-  C_NSEG,      // segments (runs of one target) of the last sorted pair list
+  C_NSEG_REP,  // runs of one target among this round's repair pairs, and the pairs
+  C_NPAIR_REP,
+  C_NSEG_REV,  // the same of its reverse-edge pairs
+  C_NPAIR_REV,
+  C_EPOCH,     // rounds begun: marks the deletes of one call
   C_QUEUE,     // work queue of the running search launch
   C_QDONE,     // waves of that launch that have left the queue
   C_RES_FREE,  // a launch's slab reservation: free-stack top before it (~0: none)
   C_RES_RET,   // and its first retired-stack slot (~0: none)
   C_NSLOW,     // targets of a maintenance phase left to its general kernel
-  C_NCOUNTERS = 32
+  C_NCOUNTERS = 48
 };
 // the repair launch's work queues, each on a line of its own after the
 // counters (atomics on one line serialize, whichever word they touch)
@@ -113,6 +117,8 @@ struct Index {
   uint32_t* retired_stack;
   unsigned long long* ctr;
   uint32_t* entries;
+  unsigned long long* dmark;    // [cap] the call that last asked to delete the id, and its first position there
+  uint32_t* tcnt;               // [cap] pairs per target while a pair list is grouped; zero otherwise
   unsigned long long* delbits;  // one bit per id: its deletion flag, for the tests that need nothing else of the word
   uint8_t* ent_x;     // uint8 rows: the entry set's rows, each byte XOR 0x80, in matrix-operand order
   int32_t* ent_norm;  // minus their squared norms (as signed bytes), padded to a multiple of 64

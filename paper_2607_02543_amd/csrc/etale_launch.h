@@ -72,17 +72,18 @@ struct MaintArgs {
   uint64_t* vis_keys;       // insert searches' expanded keys; refine's new lists
   uint32_t* vis_cnt;
   uint32_t* F;             // [n x R] forward lists
-  uint64_t* pairs;         // (target, source) keys, sorted for the apply kernels
+  uint64_t* pairs;         // (target, source) keys, grouped by target for the apply kernels
   uint32_t npairs;
+  uint32_t seg_ctr = C_NSEG_REP;  // counter with the runs of one target
   const uint32_t* dlist;   // deleted ids of the call
   uint32_t nmax;           // largest candidate count one prune sees
   uint32_t nsort;          // power of two >= nmax, >= 64
   uint32_t prune_cap;      // LDS staging rows
   uint32_t vstride;        // bytes per staged row
   uint32_t lds_per_wave;
-  const uint32_t* seg;     // starts of the runs of one target in the sorted pairs
+  const uint32_t* seg;     // starts of the runs of one target in the pairs
   uint32_t* slow = nullptr;  // repair, reverse edges: targets (run indices) left to the general kernel
-  uint32_t np_ctr = NO_CTR, np_mult = 1;  // launch-time pair count
+  uint32_t np_ctr = NO_CTR;  // launch-time pair count
   uint32_t chain = 0;      // reverse edges: cached candidate state (uint8 rows, R <= 32)
   uint32_t mx = 0;         // RobustPrune selection on the matrix cores (uint8 rows, dim <= 128, R <= 32)
   Dyn d;                   // launch-time count (n) and first id
@@ -118,18 +119,27 @@ uint32_t chain_lds_per_wave(uint32_t R, uint32_t vstride);
 uint32_t pool_lds_per_wave(uint32_t vstride);
 hipError_t launch_maint(MaintKernel which, const Index& ix, const MaintArgs& a, uint32_t nwaves,
                         uint32_t waves_per_block, hipStream_t s);
+// A phase's (target, source) pairs, grouped: `out` holds every target's pairs
+// side by side in ascending source order, `seg` where each run starts (runs in no
+// particular order). raw, rank and tlist are scratch of the pair list's size.
+struct GroupArgs {
+  uint64_t* raw;     // [n x R] the pairs as generated, KEY_NONE where there is none
+  uint64_t* out;     // [n x R]
+  uint32_t* rank;    // [n x R] arrival rank of a pair within its target
+  uint32_t* tlist;   // [n x R] the targets, as they first appear
+  uint32_t* seg;     // [n x R]
+  uint32_t nmax;     // n x R, upper bound
+  uint32_t seg_ctr, pair_ctr;
+  uint32_t reserve;  // also reserve one fresh slab and one retired slot per run
+  Dyn d;             // launch-time pair slots
+};
+// the new nodes' forward lists as pairs (w, v); ungrouped into pairs only
 hipError_t launch_reverse_pairs(const Index& ix, const MaintArgs& a, hipStream_t s);
-hipError_t launch_repair_pairs(const Index& ix, const MaintArgs& a, hipStream_t s);
-hipError_t launch_segments(const Index& ix, const uint64_t* pairs, uint32_t nmax, Dyn d, uint32_t* seg,
-                           hipStream_t s);
-// stable LSD radix sort of 64-bit keys on bits [lo, lo + nbits), preceded by
-// bits [0, low_bits) (so the order is by the high range, then the low one);
-// count read at launch time; returns the buffer (a or b) holding the result
-uint32_t sort_hist_words(uint32_t nmax);
-hipError_t launch_sort(const Index& ix, uint64_t* a, uint64_t* b, uint32_t nmax, Dyn d, int lo, int nbits,
-                       uint32_t* hist, hipStream_t s, uint64_t** result, int low_bits = 0);
-hipError_t launch_del_keys(const Index& ix, const uint32_t* ids, uint32_t n, Dyn d, uint64_t* keys, hipStream_t s);
-hipError_t launch_del_classify(const Index& ix, const uint64_t* sorted, uint32_t n, Dyn d, uint8_t* status,
+hipError_t launch_group_reverse(const Index& ix, const MaintArgs& a, const GroupArgs& g, hipStream_t s);
+// the deleted nodes' live neighbors as pairs (a, u)
+hipError_t launch_group_repair(const Index& ix, const MaintArgs& a, const GroupArgs& g, hipStream_t s);
+hipError_t launch_del_mark(const Index& ix, const uint32_t* ids, uint32_t n, Dyn d, hipStream_t s);
+hipError_t launch_del_classify(const Index& ix, const uint32_t* ids, uint32_t n, Dyn d, uint8_t* status,
                                uint32_t* dlist, hipStream_t s);
 hipError_t launch_tombstone(const Index& ix, const uint32_t* dlist, uint32_t n, Dyn d, hipStream_t s);
 hipError_t launch_dirty(const Index& ix, uint64_t n_ids, Dyn d, uint32_t* dirty, hipStream_t s);

@@ -65,3 +65,27 @@ def test_repairs_and_reverse_edges(dim, R, cap, alpha, kind):
             g.reclaim()
             assert_same_state(o, g, f"reclaim {r}")
     g.close()
+
+
+@pytest.mark.parametrize("n", [1, 255, 1000])
+def test_delete_statuses(n):
+    """Repeats, ids never handed out (repeated too) and ids already deleted, across workgroups."""
+    import torch
+    from paper_2607_02543_amd import etale
+    rng = np.random.default_rng(n)
+    o = oracle.Oracle(oracle.METRIC_L2_U8, 64, 12, 20, 1000, 30000, n_entry=16)
+    g = etale.Index(64, R=12, L_build=20, id_capacity=1000, slab_capacity=30000, max_batch=1000, n_entry=16)
+    for b in (100, 500):
+        x = rows(rng, b, 64, "clusters")
+        o.insert(x)
+        g.insert(torch.from_numpy(x).cuda())
+    for _ in range(3):
+        ids = rng.integers(0, 600, n).astype(np.uint32)
+        odd = rng.random(n)
+        ids = np.where(odd < 0.1, rng.choice([600, 650, 999, 1000, 5000, 0xFFFFFFFE, 0xFFFFFFFF], n), ids).astype(np.uint32)
+        ids = np.where(odd > 0.8, ids[rng.integers(0, n, n)], ids)
+        so = o.delete(ids)
+        sg = g.delete(torch.from_numpy(ids.astype(np.int64).astype(np.uint32).view(np.int32)).cuda()).cpu().numpy()
+        assert np.array_equal(so, sg)
+        assert_same_state(o, g, "after the deletes")
+    g.close()
