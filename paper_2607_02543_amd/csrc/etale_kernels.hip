@@ -4829,6 +4829,143 @@ __global__ void __launch_bounds__(64) k_bruteforce_f32(Index ix, const float* q,
   }
 }
 
+// ---- brute force on float rows in two passes ---------------------------------------------
+// The exact k nearest live rows of each query by (distance, id), for any number
+// of queries:
+//   k_bf_min_f32: 64 rows (one per lane) against a block of queries per wave,
+//                 only the smallest distance of each query and 64-row group is
+//                 written;
+//   k_bf_near_f32: one wave per query bounds the k-th smallest distance by the
+//                 k-th smallest group minimum and scores the rows of the groups
+//                 at or below the bound (a dozen or so) again, for their keys.
+// Both add a row's products in the order of the distance batches (lane c of G:
+// the chunks c, G + c, 2G + c in turn, then the lanes in pairs), so distances,
+// bounds and results keep its bits. The first pass is bound by FP32 issue (one
+// FMA per lane and element): a lane keeps 96 elements of its row in registers
+// and the query's come as scalars, so nothing but the FMAs is left in the loop;
+// sums that wait for their pair (rows past 96 elements) and the keys, which are
+// reduced 16 bytes at a time, are in LDS. 1,000 queries on 100,003 x 96-d rows:
+// 2.75 ms with one wave per query reading all rows (1,000 waves for the chip),
+// 0.43 ms now (first pass 346 us, 28 T FMA/s of the 39 that unpacked FP32
+// reaches; second pass 64 us).
+constexpr int BF_WAVES = 4;                        // groups per workgroup, all with the same queries
+template <int G> constexpr int bf_queries() { return G <= 16 ? 32 : 16; }  // and how many of those
+template <int G> constexpr int bf_levels() { return G <= 16 ? 1 : G == 32 ? 2 : 3; }  // log2(G / 8) waiting sums
+constexpr int BF_ROW = 68;                         // words per query in LDS: 64 lanes, padded for 16-byte reads
+constexpr uint64_t BF_SCRATCH_MAX = 256ull << 20;  // group minima per launch; more queries take further launches
+
+template <int G>
+__global__ void __launch_bounds__(64 * BF_WAVES) k_bf_min_f32(Index ix, const float* __restrict__ q, uint32_t nq,
+                                                              uint64_t n_ids, uint32_t n_grp,
+                                                              uint32_t* __restrict__ gmin) {
+  constexpr int DIM = 12 * G, NQ = bf_queries<G>(), LV = bf_levels<G>();
+  __shared__ __align__(16) uint32_t parts[BF_WAVES][LV][NQ][BF_ROW];
+  const uint32_t nqb = (nq + NQ - 1) / NQ;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), l = lane_id();
+  // an XCD's workgroups take the query blocks of its groups in turn: the rows come from its L2
+  const uint32_t j = blockIdx.x >> 3, set = j / nqb * 8u + (blockIdx.x & 7u);
+  const uint32_t grp = set * BF_WAVES + (uint32_t)wave;
+  if (grp >= n_grp) return;
+  const uint32_t q0 = j % nqb * NQ;
+  const int cnt = (int)min((uint32_t)NQ, nq - q0);
+  const float* qp = q + (size_t)q0 * DIM;
+  const uint64_t id = (uint64_t)grp * 64u + (uint64_t)l;
+  bool live = false;
+  if (id < n_ids) {
+    const uint64_t r = load_ref(ix, (uint32_t)id);
+    live = !ref_del(r) && ref_slab(r) != NONE;
+  }
+  const float4* row = reinterpret_cast<const float4*>(ix.xf + min<uint64_t>(id, n_ids - 1) * DIM);
+  uint32_t(*part)[NQ][BF_ROW] = parts[wave];
+#pragma unroll 1
+  for (int b = 0; b < G / 8; ++b) {  // lanes 8b .. 8b + 7 of the G
+    float4 x[3][8];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) x[t][c] = row[t * G + b * 8 + c];
+#pragma unroll 1
+    for (int i = 0; i < cnt; ++i) {
+      const float* y = qp + (size_t)i * DIM + b * 32;
+      float p[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        float a0 = 0.f, a1 = 0.f;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          const float* yt = y + t * 4 * G + h * 8;
+          a0 = __builtin_fmaf(yt[0], x[t][2 * h].x, a0);
+          a0 = __builtin_fmaf(yt[1], x[t][2 * h].y, a0);
+          a0 = __builtin_fmaf(yt[2], x[t][2 * h].z, a0);
+          a0 = __builtin_fmaf(yt[3], x[t][2 * h].w, a0);
+          a1 = __builtin_fmaf(yt[4], x[t][2 * h + 1].x, a1);
+          a1 = __builtin_fmaf(yt[5], x[t][2 * h + 1].y, a1);
+          a1 = __builtin_fmaf(yt[6], x[t][2 * h + 1].z, a1);
+          a1 = __builtin_fmaf(yt[7], x[t][2 * h + 1].w, a1);
+        }
+        p[h] = a0 + a1;
+      }
+      float s = (p[0] + p[1]) + (p[2] + p[3]);
+      int lv = 0;
+      for (; (b >> lv) & 1; ++lv) s = __builtin_bit_cast(float, part[lv][i][l]) + s;
+      if (b + 1 < G / 8) part[lv][i][l] = __builtin_bit_cast(uint32_t, s);
+      else part[0][i][l] = live ? fkey(1.0f - s) : D_INVALID;
+    }
+  }
+  wave_sync();
+  if (l < cnt) {
+    const uint4* v = reinterpret_cast<const uint4*>(part[0][l]);
+    uint32_t m = D_INVALID;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) m = min(m, min(min(v[i].x, v[i].y), min(v[i].z, v[i].w)));
+    gmin[(size_t)(q0 + (uint32_t)l) * n_grp + grp] = m;
+  }
+}
+
+template <int G>
+__global__ void __launch_bounds__(64) k_bf_near_f32(Index ix, const float* q, uint32_t nq, uint64_t n_ids, uint32_t k,
+                                                    uint32_t n_grp, const uint32_t* gmin, uint32_t* out_ids,
+                                                    uint32_t* out_d) {
+  __shared__ uint64_t ck[64];
+  __shared__ uint32_t ids[64];
+  const uint32_t qi = blockIdx.x;
+  const int l = lane_id();
+  using E = TravF<G, TRAV_NATIVE>;
+  const typename E::Q qv = E::load_query(q + (size_t)qi * ix.dim);
+  const uint32_t* gm = gmin + (size_t)qi * n_grp;
+  // the k-th smallest of the 64 lanes' smallest minima: k groups lie at or below it
+  uint32_t bound = D_INVALID;
+  for (uint32_t i = (uint32_t)l; i < n_grp; i += 64) bound = min(bound, gm[i]);
+  wave_sort32(bound);
+  bound = (uint32_t)__builtin_amdgcn_readlane((int)bound, (int)k - 1);
+  uint64_t best[1] = {KEY_NONE};  // the 64 smallest keys so far, ascending
+  for (uint32_t g0 = 0; g0 < n_grp; g0 += 64) {
+    const uint32_t mine = g0 + (uint32_t)l < n_grp ? gm[g0 + (uint32_t)l] : D_INVALID;
+    for (uint64_t m = ballot(g0 + (uint32_t)l < n_grp && mine <= bound); m; m &= m - 1ull) {
+      const uint64_t u = (uint64_t)(g0 + (uint32_t)__builtin_ctzll(m)) * 64u + (uint64_t)l;
+      bool ok = false;
+      if (u < n_ids) {
+        const uint64_t r = load_ref(ix, (uint32_t)u);
+        ok = !ref_del(r) && ref_slab(r) != NONE;
+      }
+      const uint64_t om = ballot(ok);
+      const int cnt = __popcll(om);
+      wave_sync();
+      if (ok) ids[lanes_below(om)] = (uint32_t)u;
+      wave_sync();
+      E::dist_batch(ix, qv, ids, cnt, ck, nullptr);
+      wave_sync();
+      uint64_t v[2] = {best[0], l < cnt ? ck[l] : KEY_NONE};
+      wave_sort_regs<2>(v);
+      best[0] = v[0];
+    }
+  }
+  if ((uint32_t)l < k) {
+    out_ids[(size_t)qi * k + l] = best[0] == KEY_NONE ? NONE : key_id(best[0]);
+    out_d[(size_t)qi * k + l] = best[0] == KEY_NONE ? 0x7F800000u : __builtin_bit_cast(uint32_t, fkey_inv(key_dist(best[0])));
+  }
+}
+
 // ---- host-side launchers ---------------------------------------------------------------------
 
 static inline unsigned blocks_for(uint64_t n, unsigned per) { return (unsigned)((n + per - 1) / per); }
@@ -5349,12 +5486,29 @@ hipError_t launch_export(const Index& ix, uint64_t n_ids, uint32_t* nbr, uint32_
 
 uint64_t bruteforce_norm_bytes(uint64_t n_ids) { return (n_ids * 4 + 255) / 256 * 256; }
 
+// float rows: queries per launch pair, so that their group minima fit the scratch
+static uint32_t bruteforce_f32_chunk(uint32_t nq, uint64_t n_ids) {
+  const uint64_t per = (n_ids + 63) / 64 * 4;
+  return (uint32_t)std::min<uint64_t>(nq, std::max<uint64_t>(1, BF_SCRATCH_MAX / std::max<uint64_t>(1, per)));
+}
+
 uint64_t bruteforce_scratch_bytes(const Index& ix, uint32_t nq, uint64_t n_ids) {
+  if (ix.metric != 0) return n_ids ? (uint64_t)bruteforce_f32_chunk(nq, n_ids) * ((n_ids + 63) / 64) * 4 : 0;
   if (ix.metric != 0 || ix.dim < 64 || ix.dim > 256) return 0;
   const uint32_t q_tiles = (nq + 15) / 16;
   const uint64_t n_chunks = std::min<uint64_t>(std::max<uint64_t>(1, (n_ids + 1023) / 1024),
                                                std::max<uint32_t>(1, (4096 + q_tiles - 1) / q_tiles));
   return bruteforce_norm_bytes(n_ids) + (uint64_t)nq * n_chunks * 4 * 16 * 8;
+}
+
+template <int G>
+static void launch_bf_f32(const Index& ix, const float* q, uint32_t nq, uint64_t n_ids, uint32_t k, uint32_t n_grp,
+                          uint32_t* gmin, uint32_t* out_ids, uint32_t* out_d, hipStream_t s) {
+  // at most 256 MiB / 4 group minima, so the grid stays far below its limit
+  const uint32_t sets = (n_grp + BF_WAVES - 1) / BF_WAVES, nqb = (nq + bf_queries<G>() - 1) / bf_queries<G>();
+  hipLaunchKernelGGL(k_bf_min_f32<G>, dim3((sets + 7) / 8 * 8 * nqb), dim3(64 * BF_WAVES), 0, s, ix, q, nq, n_ids, n_grp,
+                     gmin);
+  hipLaunchKernelGGL(k_bf_near_f32<G>, dim3(nq), dim3(64), 0, s, ix, q, nq, n_ids, k, n_grp, gmin, out_ids, out_d);
 }
 
 hipError_t launch_bruteforce(const Index& ix, const void* q, uint32_t nq, uint64_t n_ids, uint32_t k,
@@ -5384,6 +5538,21 @@ hipError_t launch_bruteforce(const Index& ix, const void* q, uint32_t nq, uint64
   } else if (ix.metric == 0) {
     hipLaunchKernelGGL(k_bruteforce_u8<16>, dim3(nq), dim3(64), 0, s, ix, (const uint8_t*)q, nq, n_ids, k, out_ids,
                        (int32_t*)out_d);
+  } else if (scratch && n_ids) {
+    const uint32_t chunk = bruteforce_f32_chunk(nq, n_ids), n_grp = (uint32_t)((n_ids + 63) / 64);
+    uint32_t* gmin = reinterpret_cast<uint32_t*>(scratch);
+    for (uint32_t c = 0; c < nq; c += chunk) {
+      const uint32_t cn = min(chunk, nq - c);
+      const float* qc = (const float*)q + (size_t)c * ix.dim;
+      uint32_t *oi = out_ids + (size_t)c * k, *od = out_d + (size_t)c * k;
+      switch (float_lanes(ix.dim, 4)) {
+        case 8: launch_bf_f32<8>(ix, qc, cn, n_ids, k, n_grp, gmin, oi, od, s); break;
+        case 16: launch_bf_f32<16>(ix, qc, cn, n_ids, k, n_grp, gmin, oi, od, s); break;
+        case 32: launch_bf_f32<32>(ix, qc, cn, n_ids, k, n_grp, gmin, oi, od, s); break;
+        case 64: launch_bf_f32<64>(ix, qc, cn, n_ids, k, n_grp, gmin, oi, od, s); break;
+        default: return hipErrorInvalidValue;
+      }
+    }
   } else {
     switch (float_lanes(ix.dim, 4)) {
       case 8: hipLaunchKernelGGL(k_bruteforce_f32<8>, dim3(nq), dim3(64), 0, s, ix, (const float*)q, nq, n_ids, k, out_ids, out_d); break;

@@ -139,3 +139,33 @@ def test_fp8_nan_codes_keep_their_value():
         assert np.isfinite(d[i]).all()
         assert np.array_equal(d[i], 1.0 - (v[ids[i]] @ q[i].astype(np.float64)) * s[ids[i]])
     g.close()
+
+
+# groups of 64 rows, 16 queries per wave and 64 per workgroup: counts inside, at
+# and past them, with deleted rows, fewer live rows than asked for, and none
+@pytest.mark.parametrize("dim,n,nq", [(96, 63, 1), (96, 700, 65), (192, 64, 16), (384, 65, 17), (768, 300, 130)])
+def test_bruteforce_equals_oracle(dim, n, nq):
+    import torch
+    rng = np.random.default_rng(n + dim)
+    o, g = make_pair(dim, 8)
+    q = lattice(rng, nq, dim)
+    qd = torch.from_numpy(q).cuda()
+
+    def check(k):
+        io, do = o.bruteforce(q, k)
+        ig, dg = g.bruteforce(qd, k)
+        assert np.array_equal(io, ig.cpu().numpy().astype(np.uint32))
+        assert np.array_equal(do, dg.cpu().numpy().astype(np.float64))
+
+    for b in range(0, n, 400):
+        x = lattice(rng, min(400, n - b), dim)
+        o.insert(x)
+        g.insert(torch.from_numpy(x).cuda())
+    for k in (1, 10, 16):
+        check(k)
+    for gone in (np.arange(0, n, 3), np.setdiff1d(np.arange(n), np.concatenate([np.arange(0, n, 3), [1, n - 1]]))):
+        for c in range(0, gone.size, 400):
+            o.delete(gone[c:c + 400].astype(np.uint32))
+            g.delete(torch.from_numpy(gone[c:c + 400].astype(np.int32)).cuda())
+        check(10)
+    g.close()
