@@ -259,7 +259,7 @@ __global__ void __launch_bounds__(1024) k_refresh_entries(Index ix, uint32_t nex
 // then for the few keys under them), so the matrix never reaches memory.
 // Start rows are in ascending id order, so the row index breaks distance ties
 // exactly as the id does.
-constexpr int SD_Q = 64, SD_E = 256, SD_KW = 4, SD_STRIDE = SD_KW + 1;  // in 16-byte words
+constexpr int SD_E = 256;  // float start rows: group slots come in blocks of this many rows
 constexpr uint32_t D_INVALID = 0xFFFFFFFFu;
 
 __device__ inline uint32_t start_id(const Index& ix, const ScanArgs& a, uint32_t e) {
@@ -381,7 +381,8 @@ constexpr int U_INVALID = (int)0x80000000;  // u of a row that is not scored
 // 64 KS bytes, a whole number of KS-slice chunks): the query operands are
 // reloaded per chunk instead of staying in registers.
 template <int PASS, bool PRE, int KS, bool CHUNKED>
-__device__ inline void scan_dist_wave_span(const Index& ix, const ScanArgs& a, uint32_t span, uint32_t q0) {
+__device__ inline void scan_dist_wave_span(const Index& ix, const ScanArgs& a, uint32_t span, uint32_t part,
+                                           uint32_t q0) {
   constexpr uint32_t CW = 64u * KS;  // bytes of a row per chunk
   const int l = lane_id();
   const uint32_t ns = a.ns, dim = ix.dim, r = (uint32_t)(l & 15), k4 = (uint32_t)(l >> 4), kc = k4 * 16u;
@@ -434,7 +435,8 @@ __device__ inline void scan_dist_wave_span(const Index& ix, const ScanArgs& a, u
       cnt[n] = 0;
     }
   }
-  uint32_t gb[8];  // SCAN_MIN / SCAN_DENSE: the span's group minima of this lane's own query
+  const uint32_t gpw = PASS == SCAN_DENSE ? a.gpw : SCAN_SPAN / 32;  // groups of this wave
+  uint32_t gb[8];  // SCAN_MIN / SCAN_DENSE: their minima of this lane's own query
 #pragma unroll
   for (int j = 0; j < 8; ++j) gb[j] = D_INVALID;
   // one group of 32 start rows: its products and results; the group's minimum
@@ -574,9 +576,20 @@ __device__ inline void scan_dist_wave_span(const Index& ix, const ScanArgs& a, u
     // unrolled, so that each minimum has a register of its own
 #pragma unroll
     for (int j = 0; j < SCAN_SPAN / 32; ++j) {
-      const uint32_t e0 = e_begin + (uint32_t)j * 32u;
-      if (e0 >= e_end) break;
+      const uint32_t e0 = e_begin + (part * gpw + (uint32_t)j) * 32u;
+      if ((uint32_t)j >= gpw || e0 >= e_end) break;
       gb[j] = group(e0);
+    }
+  }
+  if constexpr (PASS == SCAN_DENSE) {
+    if (gpw < SCAN_SPAN / 32) {  // this wave's groups of the span only
+      if (q_own < a.nq) {
+        uint32_t* gp = a.gmin + gmin_tile_slot(q_own, span, n_span) + part * gpw;
+#pragma unroll
+        for (int j = 0; j < SCAN_SPAN / 64; ++j)
+          if ((uint32_t)j < gpw) gp[j] = gb[j];
+      }
+      return;
     }
   }
   if constexpr (PASS != SCAN_FILTER) {
@@ -604,128 +617,149 @@ __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(KS <= 2 ? (PASS == SCAN_MIN ? 4 : 3) : 2))) k_scan_dist(Index ix, ScanArgs a) {
   if (gated(ix, a.d)) return;
   resolve(ix, a);
-  const uint32_t n_span = (a.ns + SCAN_SPAN - 1) / SCAN_SPAN, n_tasks = n_span * ((a.nq + SD_WT - 1) / SD_WT);
+  const uint32_t n_span = (a.ns + SCAN_SPAN - 1) / SCAN_SPAN;
+  const uint32_t parts = PASS == SCAN_DENSE ? SCAN_SPAN / 32u / a.gpw : 1u;  // waves per span
+  const uint32_t n_part = n_span * parts, n_tasks = n_part * ((a.nq + SD_WT - 1) / SD_WT);
   const uint32_t waves = gridDim.x * (blockDim.x >> 6);
   // consecutive waves take consecutive spans of one query tile
-  for (uint32_t t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); t < n_tasks; t += waves)
-    scan_dist_wave_span<PASS, PRE, KS, CHUNKED>(ix, a, t % n_span, (t / n_span) * SD_WT);
+  for (uint32_t t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); t < n_tasks; t += waves) {
+    const uint32_t sp = t % n_part;
+    scan_dist_wave_span<PASS, PRE, KS, CHUNKED>(ix, a, sp / parts, sp % parts, (t / n_part) * SD_WT);
+  }
 }
 
-// Float rows: the same 64 x 256 tiling over 16-element slices, in FP32; start
-// rows come from the traversal copy (FP8 rows as value/256, their scale
-// applied once per pair at the end).
-template <int TRAV>
-__device__ inline void scan_dist_f_tile(const Index& ix, const ScanArgs& a, uint32_t e0, uint32_t q0, float4* qt,
-                                        float4* et, float* es) {
-  const int t = (int)threadIdx.x;
-  const uint32_t ns = a.ns, dim = ix.dim;
-  const int qg = t / 32, eg = t % 32;
-  float acc[8][8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = 0.f;
-  const uint32_t my_e = e0 + (uint32_t)t;
-  const uint32_t my_eid = my_e < ns ? start_id(ix, a, my_e) : NONE;
-  es[t] = (TRAV == TRAV_FP8 && my_eid != NONE) ? ix.xs[my_eid] * 256.0f : 1.0f;
-  const uint32_t my_q = q0 + (uint32_t)(t & 63);
-  const float* qrow = nullptr;
-  if (my_q < a.nq)
-    qrow = a.mode == MODE_QUERY ? (const float*)a.q + (size_t)my_q * dim : ix.xf + (size_t)(a.first + a.qoff + my_q) * dim;
-  for (uint32_t k0 = 0; k0 < dim; k0 += 16) {
-    __syncthreads();
-    {
-      const int r = t & 63, c = t >> 6;
-      qt[r * SD_STRIDE + c] = qrow ? reinterpret_cast<const float4*>(qrow + k0)[c] : make_float4(0, 0, 0, 0);
+// Float rows: tiles of 8 QI queries x 32 EJ start rows per workgroup, staged
+// through LDS in slices of 4 KW elements, in FP32 (one FMA chain per pair in
+// element order, whatever the tile); start rows come from the traversal copy
+// (FP8 rows as value/256, their scale applied once per pair at the end). A
+// slice's loads are in flight while the one before is multiplied.
+template <int TRAV, int QI, int EJ, int KW>
+struct ScanTileF {
+  static constexpr int TQ = 8 * QI, TE = 32 * EJ, ST = KW + 1;     // LDS rows of KW 16-byte words, padded
+  static constexpr int NQ = (TQ * KW + 255) / 256, NE = TE * KW / 256;  // words per thread and slice
+  static constexpr int GL = 32 / EJ;                               // adjacent threads that hold one group of 32 rows
+  float4 qt[TQ * ST];
+  float4 et[TE * ST];
+  uint32_t eid[TE];
+  float es[TE];
+
+  // four elements of a start row, as they are in the traversal copy
+  __device__ static uint4 load_row(const Index& ix, uint32_t id, uint32_t k) {
+    if (id == NONE) return make_uint4(0, 0, 0, 0);
+    const size_t at = (size_t)id * ix.dim + k;
+    if constexpr (TRAV == TRAV_NATIVE) return *reinterpret_cast<const uint4*>(ix.xf + at);
+    if constexpr (TRAV == TRAV_BF16) {
+      const uint2 w = *reinterpret_cast<const uint2*>(ix.xb + at);
+      return make_uint4(w.x, w.y, 0, 0);
     }
-    float4 ev4[4] = {make_float4(0, 0, 0, 0), make_float4(0, 0, 0, 0), make_float4(0, 0, 0, 0),
-                     make_float4(0, 0, 0, 0)};
-    if (my_eid != NONE) {
-      if (TRAV == TRAV_NATIVE) {
-        const float4* rw = reinterpret_cast<const float4*>(ix.xf + (size_t)my_eid * dim + k0);
+    return make_uint4(*reinterpret_cast<const uint32_t*>(ix.x8 + at), 0, 0, 0);
+  }
+  __device__ static float4 decode(uint4 w) {
+    if constexpr (TRAV == TRAV_NATIVE)
+      return make_float4(__builtin_bit_cast(float, w.x), __builtin_bit_cast(float, w.y), __builtin_bit_cast(float, w.z),
+                         __builtin_bit_cast(float, w.w));
+    if constexpr (TRAV == TRAV_BF16)
+      return make_float4(__builtin_bit_cast(float, w.x << 16), __builtin_bit_cast(float, w.x & 0xFFFF0000u),
+                         __builtin_bit_cast(float, w.y << 16), __builtin_bit_cast(float, w.y & 0xFFFF0000u));
+    return make_float4(e4m3_div256(w.x & 0xFFu), e4m3_div256((w.x >> 8) & 0xFFu), e4m3_div256((w.x >> 16) & 0xFFu),
+                       e4m3_div256(w.x >> 24));
+  }
+
+  __device__ void run(const Index& ix, const ScanArgs& a, uint32_t e0, uint32_t q0) {
+    const int t = (int)threadIdx.x;
+    const uint32_t ns = a.ns, dim = ix.dim;
+    const int qg = t / 32, eg = t % 32;
+    __syncthreads();  // the tile before has been read
+    if (t < TE) {
+      const uint32_t e = e0 + (uint32_t)t, id = e < ns ? start_id(ix, a, e) : NONE;
+      eid[t] = id;
+      es[t] = (TRAV == TRAV_FP8 && id != NONE) ? ix.xs[id] * 256.0f : 1.0f;
+    }
+    __syncthreads();
+    const float* qb = a.mode == MODE_QUERY ? (const float*)a.q : ix.xf + (size_t)(a.first + a.qoff) * dim;
+    const float* qrow[NQ];  // null past the tile or the launch's queries
 #pragma unroll
-        for (int c = 0; c < 4; ++c) ev4[c] = rw[c];
-      } else if (TRAV == TRAV_BF16) {
-        const uint4* rw = reinterpret_cast<const uint4*>(ix.xb + (size_t)my_eid * dim + k0);
+    for (int n = 0; n < NQ; ++n) {
+      const int r = (t + 256 * n) / KW;
+      qrow[n] = r < TQ && q0 + (uint32_t)r < a.nq ? qb + (size_t)(q0 + (uint32_t)r) * dim + (t % KW) * 4 : nullptr;
+    }
+    uint32_t id[NE];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const uint4 w = rw[h];
-          const uint32_t wd[4] = {w.x, w.y, w.z, w.w};
-          float f[8];
+    for (int n = 0; n < NE; ++n) id[n] = eid[(t + 256 * n) / KW];
+    float4 qn[NQ];
+    uint4 en[NE];
+    auto fetch = [&](uint32_t k0) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            f[2 * e] = __builtin_bit_cast(float, wd[e] << 16);
-            f[2 * e + 1] = __builtin_bit_cast(float, wd[e] & 0xFFFF0000u);
+      for (int n = 0; n < NQ; ++n)
+        qn[n] = qrow[n] ? *reinterpret_cast<const float4*>(qrow[n] + k0) : make_float4(0, 0, 0, 0);
+#pragma unroll
+      for (int n = 0; n < NE; ++n) en[n] = load_row(ix, id[n], k0 + (uint32_t)(t % KW) * 4u);
+    };
+    float acc[QI][EJ];
+#pragma unroll
+    for (int i = 0; i < QI; ++i)
+#pragma unroll
+      for (int j = 0; j < EJ; ++j) acc[i][j] = 0.f;
+    fetch(0);
+    for (uint32_t k0 = 0; k0 < dim; k0 += 4 * KW) {
+      __syncthreads();
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+        if (TQ * KW % 256 == 0 || t + 256 * n < TQ * KW) qt[(t + 256 * n) / KW * ST + t % KW] = qn[n];
+#pragma unroll
+      for (int n = 0; n < NE; ++n) et[(t + 256 * n) / KW * ST + t % KW] = decode(en[n]);
+      __syncthreads();
+      if (k0 + 4 * KW < dim) fetch(k0 + 4 * KW);
+#pragma unroll
+      for (int c = 0; c < KW; ++c) {
+        float4 qv[QI], ev[EJ];
+#pragma unroll
+        for (int i = 0; i < QI; ++i) qv[i] = qt[(qg * QI + i) * ST + c];
+#pragma unroll
+        for (int j = 0; j < EJ; ++j) ev[j] = et[(eg + 32 * j) * ST + c];
+#pragma unroll
+        for (int i = 0; i < QI; ++i)
+#pragma unroll
+          for (int j = 0; j < EJ; ++j) {
+            float x = acc[i][j];
+            x = __builtin_fmaf(qv[i].x, ev[j].x, x);
+            x = __builtin_fmaf(qv[i].y, ev[j].y, x);
+            x = __builtin_fmaf(qv[i].z, ev[j].z, x);
+            acc[i][j] = __builtin_fmaf(qv[i].w, ev[j].w, x);
           }
-          ev4[2 * h] = make_float4(f[0], f[1], f[2], f[3]);
-          ev4[2 * h + 1] = make_float4(f[4], f[5], f[6], f[7]);
-        }
-      } else {
-        const uint4 w = *reinterpret_cast<const uint4*>(ix.x8 + (size_t)my_eid * dim + k0);
-        const uint32_t wd[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          ev4[e] = make_float4(e4m3_div256(wd[e] & 0xFFu), e4m3_div256((wd[e] >> 8) & 0xFFu),
-                               e4m3_div256((wd[e] >> 16) & 0xFFu), e4m3_div256(wd[e] >> 24));
       }
     }
+    // group minima: the 32 start rows e0 + GL (eg / GL) + {0 .. GL - 1} + 32 j form
+    // group e0 / 32 + eg / GL, reduced over the GL adjacent threads that hold them
 #pragma unroll
-    for (int c = 0; c < 4; ++c) et[t * SD_STRIDE + c] = ev4[c];
-    __syncthreads();
+    for (int i = 0; i < QI; ++i) {
+      const uint32_t qi = q0 + (uint32_t)(qg * QI + i);
+      const uint32_t self = a.mode == MODE_BOOT ? a.qoff + qi : NONE;
+      uint32_t g = D_INVALID;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float4 qv[8], ev[8];
+      for (int j = 0; j < EJ; ++j) {
+        const uint32_t e = e0 + (uint32_t)(eg + 32 * j);
+        const float d = 1.0f - es[eg + 32 * j] * acc[i][j];
+        const uint32_t key = e == self || e >= ns ? D_INVALID : fkey(d);
+        g = min(g, key);
+        if (qi < a.nq && e < ns) a.dist[(size_t)qi * ns + e] = key;
+      }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) qv[i] = qt[(qg * 8 + i) * SD_STRIDE + c];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) ev[j] = et[(eg + 32 * j) * SD_STRIDE + c];
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float x = acc[i][j];
-          x = __builtin_fmaf(qv[i].x, ev[j].x, x);
-          x = __builtin_fmaf(qv[i].y, ev[j].y, x);
-          x = __builtin_fmaf(qv[i].z, ev[j].z, x);
-          acc[i][j] = __builtin_fmaf(qv[i].w, ev[j].w, x);
-        }
+      for (int o = 1; o < GL; o <<= 1) g = min(g, (uint32_t)__shfl_xor((int)g, o, 64));
+      if (qi < a.nq && eg % GL == 0) a.gmin[(size_t)qi * a.g_stride + (e0 >> 5) + (uint32_t)(eg / GL)] = g;
     }
   }
-  __syncthreads();
-  // group minima: the 32 start rows e0 + 4 (eg / 4) + {0..3} + 32 j form group
-  // e0 / 32 + eg / 4 (8 group slots per 256-row tile), reduced over the four
-  // adjacent threads that hold them
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const uint32_t qi = q0 + (uint32_t)(qg * 8 + i);
-    const uint32_t self = a.mode == MODE_BOOT ? a.qoff + qi : NONE;
-    uint32_t g = D_INVALID;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t e = e0 + (uint32_t)(eg + 32 * j);
-      const float d = 1.0f - es[eg + 32 * j] * acc[i][j];
-      const uint32_t key = e == self || e >= ns ? D_INVALID : fkey(d);
-      g = min(g, key);
-      if (qi < a.nq && e < ns) a.dist[(size_t)qi * ns + e] = key;
-    }
-    g = min(g, (uint32_t)__shfl_xor((int)g, 1, 64));
-    g = min(g, (uint32_t)__shfl_xor((int)g, 2, 64));
-    if (qi < a.nq && (eg & 3) == 0) a.gmin[(size_t)qi * a.g_stride + (e0 >> 5) + (uint32_t)(eg >> 2)] = g;
-  }
-}
+};
 
-template <int TRAV>
+template <int TRAV, int QI, int EJ, int KW>
 __global__ void __launch_bounds__(256) k_scan_dist_f(Index ix, ScanArgs a) {
-  __shared__ float4 qt[SD_Q * SD_STRIDE];
-  __shared__ float4 et[SD_E * SD_STRIDE];
-  __shared__ float es[SD_E];
+  using T = ScanTileF<TRAV, QI, EJ, KW>;
+  __shared__ T tile;
   if (gated(ix, a.d)) return;
   resolve(ix, a);
-  const uint32_t n_et = (a.ns + SD_E - 1) / SD_E, n_tiles = n_et * ((a.nq + SD_Q - 1) / SD_Q);
-  for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    __syncthreads();
-    scan_dist_f_tile<TRAV>(ix, a, (tile % n_et) * SD_E, (tile / n_et) * SD_Q, qt, et, es);
-  }
+  // whole 256-row blocks, so that every group slot is written
+  const uint32_t n_et = (a.ns + SD_E - 1) / SD_E * (SD_E / T::TE), n_tiles = n_et * ((a.nq + T::TQ - 1) / T::TQ);
+  for (uint32_t i = blockIdx.x; i < n_tiles; i += gridDim.x) tile.run(ix, a, (i % n_et) * T::TE, (i / n_et) * T::TQ);
 }
 
 // One wave per query: the exact L smallest (distance, row) pairs of its
@@ -927,7 +961,8 @@ __global__ void __launch_bounds__(256) k_scan_select(Index ix, ScanArgs a, uint3
   scan_select_one(ix, a, qi, reinterpret_cast<uint64_t*>(smem + (size_t)(threadIdx.x >> 6) * 8 * sel_cap), sel_cap);
 }
 
-// uint8 rows, in four launches that never write the distance matrix: group
+// uint8 rows with many query-row pairs, in four launches that never write the
+// distance matrix: group
 // minima (k_scan_dist<SCAN_MIN>), each query's bound (k_scan_bound), the keys
 // at or below it (k_scan_dist<SCAN_FILTER>), and their sort (k_scan_final).
 // A query whose keys overflow its list (heavy ties at the bound) has its
@@ -967,6 +1002,50 @@ __device__ inline void scan_dense_row_u8(const Index& ix, const ScanArgs& a, uin
   }
   __threadfence_block();
   wave_sync();
+}
+
+// the n keys of sel sorted, query qi's L smallest written as its initial list
+__device__ inline void scan_sort_keys(const Index& ix, const ScanArgs& a, uint32_t qi, uint64_t* sel, uint32_t n) {
+  const int l = lane_id();
+  const int np = next_pow2_ge64((int)n);
+  for (int i = (int)n + l; i < np; i += 64) sel[i] = KEY_NONE;
+  wave_sync();
+  const uint32_t cnt = min(n, scan_need(a, qi));
+  uint64_t* out = a.out_keys + (size_t)qi * a.out_stride;
+  if (np <= 128) {
+    // up to 128 keys: sorted in registers, two per lane
+    uint64_t v[2] = {sel[l], np > 64 ? sel[64 + l] : KEY_NONE};
+    if (np > 64) {
+      wave_sort_regs<2>(v);
+    } else {
+      uint64_t (&v1)[1] = *reinterpret_cast<uint64_t(*)[1]>(&v[0]);
+      wave_sort_regs<1>(v1);
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      if ((uint32_t)(s * 64 + l) < cnt) out[s * 64 + l] = make_key(key_dist(v[s]), start_id(ix, a, key_id(v[s])));
+  } else if (np <= 512) {
+    // up to 512 keys: sorted in registers, four or eight per lane
+    uint64_t v[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) v[s] = s * 64 < np ? sel[s * 64 + l] : KEY_NONE;
+    if (np <= 256) {
+      uint64_t (&v4)[4] = *reinterpret_cast<uint64_t(*)[4]>(&v[0]);
+      wave_sort_regs<4>(v4);
+    } else {
+      wave_sort_regs<8>(v);
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      if ((uint32_t)(s * 64 + l) < cnt) out[s * 64 + l] = make_key(key_dist(v[s]), start_id(ix, a, key_id(v[s])));
+  } else {
+    wave_bitonic_sort(sel, np);
+    for (uint32_t i = (uint32_t)l; i < cnt; i += 64) {
+      const uint64_t k = sel[i];
+      out[i] = make_key(key_dist(k), start_id(ix, a, key_id(k)));
+    }
+  }
+  if (l == 0) a.out_n[qi] = cnt;
 }
 
 __global__ void __launch_bounds__(256) k_scan_final(Index ix, ScanArgs a, uint32_t sel_cap) {
@@ -1018,45 +1097,113 @@ __global__ void __launch_bounds__(256) k_scan_final(Index ix, ScanArgs a, uint32
     for (uint32_t j = EARLY / 4; j < ck[k]; ++j) sel[off + j] = src[4 * j + (uint32_t)k];
     off += ck[k];
   }
-  const int np = next_pow2_ge64((int)n);
-  for (int i = (int)n + l; i < np; i += 64) sel[i] = KEY_NONE;
-  wave_sync();
-  const uint32_t cnt = min(n, scan_need(a, qi));
-  uint64_t* out = a.out_keys + (size_t)qi * a.out_stride;
-  if (np <= 128) {
-    // up to 128 keys: sorted in registers, two per lane
-    uint64_t v[2] = {sel[l], np > 64 ? sel[64 + l] : KEY_NONE};
-    if (np > 64) {
-      wave_sort_regs<2>(v);
-    } else {
-      uint64_t (&v1)[1] = *reinterpret_cast<uint64_t(*)[1]>(&v[0]);
-      wave_sort_regs<1>(v1);
+  scan_sort_keys(ix, a, qi, sel, n);
+}
+
+// Lists of at most SCAN_FILTER_L_MAX from a written distance matrix (float rows;
+// uint8 rows as launch_scan decides): one wave per query reads its row once, 64
+// distances per lane in flight (4,096 rows), keeps those at or below the bound
+// and sorts them. The bound is the L-th smallest minimum of a group of rows:
+// groups of 32 from the scoring kernel, or of 4 from the registers where there
+// are fewer than two groups of 32 per list entry (the bound then admits most
+// rows: 2,500 rows, L = 128, 33 queries: whole search 223 us against 161). Bound
+// by latency: its loads, then about 20 dependent bisection steps and the sort.
+// The general selection with its passes over the row in memory stays for rows
+// whose keys overflow (heavy ties) and for longer lists.
+struct __attribute__((packed, aligned(4))) U4 { uint32_t v[4]; };
+__global__ void __launch_bounds__(64) k_scan_pick(Index ix, ScanArgs a, uint32_t sel_cap) {
+  extern __shared__ __align__(16) char smem[];
+  if (gated(ix, a.d)) return;
+  resolve(ix, a);
+  const uint32_t qi = blockIdx.x;
+  if (qi >= a.nq) return;
+  uint64_t* sel = reinterpret_cast<uint64_t*>(smem);
+  const int l = lane_id();
+  const uint32_t ns = a.ns, need_all = scan_need(a, qi);
+  const uint32_t* D = a.dist + (size_t)qi * ns;
+  constexpr int UN = 16;  // 4,096 rows per step
+  U4 w[UN];
+  auto load = [&](uint32_t base) {
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const uint32_t i = base + (uint32_t)(u * 64 + l) * 4u;
+      w[u] = U4{{D_INVALID, D_INVALID, D_INVALID, D_INVALID}};
+      if (i + 3 < ns) {
+        w[u] = *reinterpret_cast<const U4*>(D + i);
+      } else if (i < ns) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+          if (i + (uint32_t)j < ns) w[u].v[j] = D[i + (uint32_t)j];
+      }
     }
+  };
+  load(0);  // in flight with the bound's group minima
+  uint32_t hi = 0;
+  if (ns <= UN * 256u && ns < 64u * need_all) {
+    // too few groups of 32 rows for a close bound: minima of four rows, in registers
+    uint32_t lo = D_INVALID, valid = 0, gv[UN];
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-      if ((uint32_t)(s * 64 + l) < cnt) out[s * 64 + l] = make_key(key_dist(v[s]), start_id(ix, a, key_id(v[s])));
-  } else if (np <= 512) {
-    // up to 512 keys: sorted in registers, four or eight per lane
-    uint64_t v[8];
-#pragma unroll
-    for (int s = 0; s < 8; ++s) v[s] = s * 64 < np ? sel[s * 64 + l] : KEY_NONE;
-    if (np <= 256) {
-      uint64_t (&v4)[4] = *reinterpret_cast<uint64_t(*)[4]>(&v[0]);
-      wave_sort_regs<4>(v4);
-    } else {
-      wave_sort_regs<8>(v);
+    for (int u = 0; u < UN; ++u) {
+      gv[u] = min(min(w[u].v[0], w[u].v[1]), min(w[u].v[2], w[u].v[3]));
+      if (gv[u] != D_INVALID) {
+        lo = min(lo, gv[u]);
+        hi = max(hi, gv[u]);
+        ++valid;
+      }
     }
+    for (int o = 32; o > 0; o >>= 1) {
+      lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+      hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+      valid += (uint32_t)__shfl_xor((int)valid, o, 64);
+    }
+    lo = bcast(lo);
+    hi = bcast(hi);
+    if (bcast(valid) < need_all) {
+      hi = D_INVALID - 1;
+    } else {
+      while (lo < hi) {
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        uint32_t c = 0;
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
-      if ((uint32_t)(s * 64 + l) < cnt) out[s * 64 + l] = make_key(key_dist(v[s]), start_id(ix, a, key_id(v[s])));
-  } else {
-    wave_bitonic_sort(sel, np);
-    for (uint32_t i = (uint32_t)l; i < cnt; i += 64) {
-      const uint64_t k = sel[i];
-      out[i] = make_key(key_dist(k), start_id(ix, a, key_id(k)));
+        for (int u = 0; u < UN; ++u) c += (uint32_t)__popcll(ballot(gv[u] <= mid));
+        if (c >= need_all) hi = mid;
+        else lo = mid + 1;
+      }
+    }
+  } else if (need_all) {
+    hi = scan_bound_one(a, qi, need_all);
+  }
+  uint32_t n = 0;
+  for (uint32_t base = 0; need_all && base < ns; base += UN * 256u) {
+    if (base) load(base);
+    uint32_t c = 0;
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c += w[u].v[j] <= hi ? 1u : 0u;
+    uint32_t off = c;  // inclusive prefix over the lanes
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t v = (uint32_t)__shfl_up((int)off, (unsigned)o, 64);
+      if (l >= o) off += v;
+    }
+    const uint32_t tot = (uint32_t)__shfl((int)off, 63, 64);
+    uint32_t pos = n + off - c;
+    n += tot;
+    if (n > sel_cap) break;
+    if (c) {
+#pragma unroll
+      for (int u = 0; u < UN; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (w[u].v[j] <= hi) sel[pos++] = make_key(w[u].v[j], base + (uint32_t)(u * 64 + l) * 4u + (uint32_t)j);
     }
   }
-  if (l == 0) a.out_n[qi] = cnt;
+  if (n > sel_cap) {  // heavy ties at the bound
+    wave_sync();
+    scan_select_one(ix, a, qi, sel, sel_cap);
+    return;
+  }
+  scan_sort_keys(ix, a, qi, sel, n);
 }
 
 // keys per wave: the compacted rows, or the L selected ones
@@ -5120,14 +5267,33 @@ static void launch_scan_dist(const Index& ix, const ScanArgs& a, dim3 grid, hipS
     hipLaunchKernelGGL((k_scan_dist<PASS, PRE, 4, true>), grid, dim3(256), 0, s, ix, a);
 }
 
+template <int TRAV, int QI, int EJ, int KW>
+static bool launch_scan_tile_f(const Index& ix, const ScanArgs& a, uint64_t least, hipStream_t s) {
+  using T = ScanTileF<TRAV, QI, EJ, KW>;
+  const uint64_t tiles = (uint64_t)blocks_for(a.ns ? a.ns : 1u, SD_E) * (SD_E / T::TE) * blocks_for(a.nq, T::TQ);
+  if (tiles < least) return false;
+  const dim3 grid(tiles < 2 * PERSIST_BLOCKS ? (unsigned)tiles : 2 * PERSIST_BLOCKS);
+  hipLaunchKernelGGL((k_scan_dist_f<TRAV, QI, EJ, KW>), grid, dim3(256), 0, s, ix, a);
+  return true;
+}
+// The largest tile (most products per LDS read) that still gives every CU one:
+// a smaller tile costs a quarter more reads per product, an idle CU all of its
+// rate. 2,000 queries on 1,024 x 768-d FP8 rows are 128 tiles of 64 x 256 (151
+// us), 504 of 32 x 128 (66 us); 100 queries on bf16 rows 8 against 112 of 16 x 64
+// (146 against 22 us); with 512 or 1,024 tiles asked for the same within 1%.
+template <int TRAV>
+static void launch_scan_dist_f(const Index& ix, const ScanArgs& a, hipStream_t s) {
+  constexpr uint64_t CUS = 256;
+  if (launch_scan_tile_f<TRAV, 8, 8, 4>(ix, a, CUS, s) || launch_scan_tile_f<TRAV, 4, 4, 8>(ix, a, CUS, s)) return;
+  (void)launch_scan_tile_f<TRAV, 2, 2, 8>(ix, a, 0, s);
+}
+
 hipError_t launch_scan(const Index& ix, const ScanArgs& args, hipStream_t s, hipEvent_t after_dist) {
   if (args.nq == 0) return hipSuccess;
   ScanArgs a = args;
   a.g_rows = ix.metric == 0 ? (uint32_t)SD_WT : (uint32_t)SD_E;
   a.g_stride = blocks_for(a.ns ? a.ns : 1u, a.g_rows) * (a.g_rows / 32);
   // shapes from the upper bounds; the kernels resolve the launch-time counts
-  const uint64_t tiles = (uint64_t)blocks_for(a.ns ? a.ns : 1u, SD_E) * blocks_for(a.nq, SD_Q);
-  const dim3 dgrid(tiles < 2 * PERSIST_BLOCKS ? (unsigned)tiles : 2 * PERSIST_BLOCKS);
   const uint32_t cap = scan_select_keys(a.L);
   const dim3 grid(blocks_for(a.nq, 4)), blk(256);
   const size_t lds = 4 * scan_select_lds_per_wave(a.L);
@@ -5139,17 +5305,32 @@ hipError_t launch_scan(const Index& ix, const ScanArgs& args, hipStream_t s, hip
     const uint64_t wg = (wt + 3) / 4;
     const dim3 tgrid(wg < 4 * PERSIST_BLOCKS ? (unsigned)wg : 4 * PERSIST_BLOCKS);
     const bool pre = a.mode != MODE_BOOT && ix.ent_x && ix.ent_norm;
-    if (a.L > SCAN_FILTER_L_MAX) {
-      // long lists: the bound admits a large share of the rows, so the matrix is written
+    const bool few = a.L <= SCAN_FILTER_L_MAX && ((uint64_t)a.nq * a.ns <= SCAN_DENSE_PAIRS || a.ns <= 32u * a.L);
+    a.gpw = SCAN_SPAN / 32;
+    if (few || a.L > SCAN_FILTER_L_MAX) {
+      // The distance matrix is written: two launches instead of four. Few pairs: the
+      // matrix is small and the launches count (search of 1 query, 8,192 rows, L = 64:
+      // 75 us against 87; 1,000 queries: 118 against 120; 2,000: 147 against 136; with
+      // 2,500 rows 4,096 queries: 150 against 163, 10,000: 329 each). Lists of at least
+      // a 32nd of the rows: a bound from groups of 32 admits nearly all rows (4,096
+      // rows, L = 128: 160 against 260 us at 33 queries, 618 against 961 at 10,000);
+      // lists past SCAN_FILTER_L_MAX admit a large share always.
+      // A span is split over up to eight waves until the chip has SCAN_WAVES of them
+      while (a.gpw > 1 && wt * (SCAN_SPAN / 32 / a.gpw) < SCAN_WAVES) a.gpw >>= 1;
+      const uint64_t dg = (wt * (SCAN_SPAN / 32 / a.gpw) + 3) / 4;
+      const dim3 sgrid(dg < 4 * PERSIST_BLOCKS ? (unsigned)dg : 4 * PERSIST_BLOCKS);
       if (pre)
-        launch_scan_dist<SCAN_DENSE, true>(ix, a, tgrid, s);
+        launch_scan_dist<SCAN_DENSE, true>(ix, a, sgrid, s);
       else
-        launch_scan_dist<SCAN_DENSE, false>(ix, a, tgrid, s);
+        launch_scan_dist<SCAN_DENSE, false>(ix, a, sgrid, s);
       if (after_dist) {
         const hipError_t e = hipEventRecord(after_dist, s);
         if (e != hipSuccess) return e;
       }
-      hipLaunchKernelGGL(k_scan_select, grid, blk, lds, s, ix, a, cap);
+      if (few)
+        hipLaunchKernelGGL(k_scan_pick, dim3(a.nq), dim3(64), 8 * cap, s, ix, a, cap);
+      else
+        hipLaunchKernelGGL(k_scan_select, grid, blk, lds, s, ix, a, cap);
       return hipGetLastError();
     }
     if (!a.bound || !a.ncand || !a.cand) return hipErrorInvalidValue;
@@ -5173,18 +5354,18 @@ hipError_t launch_scan(const Index& ix, const ScanArgs& args, hipStream_t s, hip
     return hipGetLastError();
   } else {
     const int trav = a.mode == MODE_BOOT ? TRAV_NATIVE : a.trav;
-    if (trav == TRAV_NATIVE)
-      hipLaunchKernelGGL(k_scan_dist_f<TRAV_NATIVE>, dgrid, dim3(256), 0, s, ix, a);
-    else if (trav == TRAV_BF16)
-      hipLaunchKernelGGL(k_scan_dist_f<TRAV_BF16>, dgrid, dim3(256), 0, s, ix, a);
-    else
-      hipLaunchKernelGGL(k_scan_dist_f<TRAV_FP8>, dgrid, dim3(256), 0, s, ix, a);
+    if (trav == TRAV_NATIVE) launch_scan_dist_f<TRAV_NATIVE>(ix, a, s);
+    else if (trav == TRAV_BF16) launch_scan_dist_f<TRAV_BF16>(ix, a, s);
+    else launch_scan_dist_f<TRAV_FP8>(ix, a, s);
   }
   if (after_dist) {
     const hipError_t e = hipEventRecord(after_dist, s);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_scan_select, grid, blk, lds, s, ix, a, cap);
+  if (a.L <= SCAN_FILTER_L_MAX)
+    hipLaunchKernelGGL(k_scan_pick, dim3(a.nq), dim3(64), 8 * cap, s, ix, a, cap);
+  else
+    hipLaunchKernelGGL(k_scan_select, grid, blk, lds, s, ix, a, cap);
   return hipGetLastError();
 }
 
@@ -5494,7 +5675,7 @@ static uint32_t bruteforce_f32_chunk(uint32_t nq, uint64_t n_ids) {
 
 uint64_t bruteforce_scratch_bytes(const Index& ix, uint32_t nq, uint64_t n_ids) {
   if (ix.metric != 0) return n_ids ? (uint64_t)bruteforce_f32_chunk(nq, n_ids) * ((n_ids + 63) / 64) * 4 : 0;
-  if (ix.metric != 0 || ix.dim < 64 || ix.dim > 256) return 0;
+  if (ix.dim < 64 || ix.dim > 256) return 0;
   const uint32_t q_tiles = (nq + 15) / 16;
   const uint64_t n_chunks = std::min<uint64_t>(std::max<uint64_t>(1, (n_ids + 1023) / 1024),
                                                std::max<uint32_t>(1, (4096 + q_tiles - 1) / q_tiles));

@@ -41,6 +41,10 @@ struct SearchArgs {
 // per query before the dense fallback, and the longest list selected from
 // those keys (longer lists write the distance matrix)
 constexpr uint32_t SCAN_SPAN = 256, SCAN_KEYS_Q = 2048, SCAN_CAND_CAP = 1024, SCAN_FILTER_L_MAX = 128;
+// query-row pairs up to which the distance matrix is written once instead, and
+// the waves one dense pass is split into (2,048: two per SIMD)
+constexpr uint64_t SCAN_DENSE_PAIRS = 8ull << 20;
+constexpr uint32_t SCAN_WAVES = 2048;
 // bytes of the uint8 entry set's operand-ordered copy: n entries padded to a
 // multiple of 32, rows padded to whole 64-byte slices
 inline uint64_t ent_copy_bytes(uint64_t n, uint32_t dim) { return (n + 31) / 32 * 32 * ((dim + 63) / 64 * 64); }
@@ -55,6 +59,7 @@ struct ScanArgs {
   uint32_t* gmin;      // [nq x g_stride] smallest distance of each group of start rows
   uint32_t g_stride;   // group slots per query (upper bound over the launch-time ns)
   uint32_t g_rows;     // start rows per scoring tile; each tile has g_rows / 32 group slots
+  uint32_t gpw;        // uint8 rows, dense: groups of 32 start rows per wave (8, 4, 2 or 1)
   uint32_t* bound;     // uint8 rows: [nq] bound on the L-th smallest distance
   uint32_t* ncand;     // uint8 rows: [nq x spans] rows at or below the bound in each span of start rows,
                        // one byte per scoring lane
