@@ -78,6 +78,7 @@ enum Counter {
   C_QDONE,     // waves of that launch that have left the queue
   C_RES_FREE,  // a launch's slab reservation: free-stack top before it (~0: none)
   C_RES_RET,   // and its first retired-stack slot (~0: none)
+  C_RDONE,     // workgroups of the running recycle launch that have copied
   C_NSLOW,     // targets of a maintenance phase left to its general kernel
   C_NCOUNTERS = 48
 };
@@ -774,12 +775,14 @@ __device__ inline void finish_slabs_block(const Index& ix, SlabCursor& c, Counte
 constexpr uint64_t REF_UNREAD = ~0ull;
 
 // snap0: u's reference word as the caller read it (REF_UNREAD: read it here);
-// a failed compare-and-swap reads it afresh for the next attempt.
+// a failed compare-and-swap reads it afresh for the next attempt. tried:
+// attempts the caller has made already.
 __device__ inline bool publish(const Index& ix, uint32_t u, const uint32_t* ids, const uint32_t* d, uint32_t n,
-                               Counter which, SlabCursor* cur = nullptr, uint64_t snap0 = REF_UNREAD) {
+                               Counter which, SlabCursor* cur = nullptr, uint64_t snap0 = REF_UNREAD,
+                               uint32_t tried = 0) {
   const int l = lane_id();
   const uint32_t R = ix.R;
-  for (uint32_t attempt = 0; attempt < ix.publish_attempts; ++attempt) {
+  for (uint32_t attempt = tried; attempt < ix.publish_attempts; ++attempt) {
     const uint64_t snap = attempt == 0 && snap0 != REF_UNREAD ? snap0 : bcast64(load_ref(ix, u));
     uint32_t s = 0;
     if (cur && cur->free_left) {

@@ -36,21 +36,40 @@ __global__ void k_init(Index ix) {
     for (uint32_t i = threadIdx.x; i < CTR_WORDS; i += blockDim.x) ix.ctr[i] = i == C_FREE_TOP ? ix.P : 0ull;
 }
 
-// End of a launch epoch: the retired stack joins the free stack (Lemma 1).
-// The epoch's end (Lemma 1): retired slabs rejoin the free stack. Many
-// workgroups copy; a one-thread launch after them moves the counters.
-__global__ void __launch_bounds__(256) k_recycle(Index ix) {
-  const uint64_t n = ix.ctr[C_RETIRED_TOP];
-  const uint64_t f = ix.ctr[C_FREE_TOP];
-  if (f + n > ix.P) return;  // reported by k_recycle_commit
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    ix.free_stack[f + i] = ix.retired_stack[i];
-}
+// The epoch's end (Lemma 1): retired slabs rejoin the free stack. As many
+// workgroups as there are slabs for copy; the last of them to finish moves the
+// counters. Bound by latency: a second launch for the counters cost 4 us and the
+// gap before it, three times per round with reclaim.
+constexpr uint32_t RECYCLE_CHUNK = 1024, RECYCLE_BLOCKS = 256;
 
-__global__ void k_recycle_commit(Index ix) {
+__global__ void __launch_bounds__(256) k_recycle(Index ix) {
+  __shared__ bool last;
   const uint64_t n = ix.ctr[C_RETIRED_TOP];
   const uint64_t f = ix.ctr[C_FREE_TOP];
-  if (f + n > ix.P) {
+  const uint32_t blocks = (uint32_t)min<uint64_t>(RECYCLE_BLOCKS, max<uint64_t>(1, (n + RECYCLE_CHUNK - 1) / RECYCLE_CHUNK));
+  if (blockIdx.x >= blocks) return;
+  const bool fits = f + n <= ix.P;
+  if (fits)
+    for (uint64_t c = (uint64_t)blockIdx.x * RECYCLE_CHUNK; c < n; c += (uint64_t)blocks * RECYCLE_CHUNK) {
+      uint32_t v[RECYCLE_CHUNK / 256];
+#pragma unroll
+      for (uint32_t j = 0; j < RECYCLE_CHUNK / 256; ++j) {
+        const uint64_t i = c + j * 256u + threadIdx.x;
+        v[j] = i < n ? ix.retired_stack[i] : 0u;
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < RECYCLE_CHUNK / 256; ++j) {
+        const uint64_t i = c + j * 256u + threadIdx.x;
+        if (i < n) ix.free_stack[f + i] = v[j];
+      }
+    }
+  // every workgroup that counts here has read both counters
+  __syncthreads();
+  if (threadIdx.x == 0) last = blocks == 1 || atomicAdd(&ix.ctr[C_RDONE], 1ull) == blocks - 1;
+  __syncthreads();
+  if (!last || threadIdx.x != 0) return;
+  if (blocks > 1) ix.ctr[C_RDONE] = 0;
+  if (!fits) {
     atomicOr(&ix.ctr[C_ERROR], (unsigned long long)ERR_POOL_OVERFLOW);
     return;
   }
@@ -125,13 +144,17 @@ __global__ void k_round_gate(Index ix, uint32_t tombstone_only, uint32_t boot_ma
   if (status) status[0] = st;
 }
 
-// reclaim: compaction republishes every dirty node, so it needs that many slabs
+__device__ inline void reserve_launch(const Index& ix, uint64_t n);
+
+// reclaim: compaction republishes every dirty node, so it needs that many
+// slabs, which are reserved here for the whole launch
 __global__ void k_reclaim_gate(Index ix, int32_t* status) {
   if (threadIdx.x != 0) return;
   const uint64_t gate = ix.ctr[C_R_GATE];
   if (gate & G_FAIL) return;
   const bool ok = ix.ctr[C_FREE_TOP] >= ix.ctr[C_DIRTY];
-  if (!ok) ix.ctr[C_R_GATE] = gate | G_RFAIL;
+  if (ok) reserve_launch(ix, ix.ctr[C_DIRTY]);
+  else ix.ctr[C_R_GATE] = gate | G_RFAIL;
   if (status) status[1] = ok ? 0 : ST_EPOOL;
 }
 
@@ -3134,7 +3157,11 @@ __device__ inline void refine_one(const Index& ix, const MaintArgs& a, MaintLds&
 
 // Refine reads every list as it stands when the pass starts: the new lists
 // are computed into the insert searches' scratch first (k_refine), then
-// published (k_refine_publish).
+// published (k_refine_publish, in workgroups of 16 waves: each reserves its slabs
+// with two atomics on the same words, which the chip takes one after the other;
+// 10,000 new nodes: 61 us in workgroups of four, 23 now).
+constexpr uint32_t RP_WAVES = 16;
+
 template <class P>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P::WPE))) k_refine(Index ix, MaintArgs a) {
   extern __shared__ __align__(16) char smem[];
@@ -3147,7 +3174,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P::WPE
   }
 }
 
-__global__ void __launch_bounds__(256) k_refine_publish(Index ix, MaintArgs a) {
+__global__ void __launch_bounds__(64 * RP_WAVES) k_refine_publish(Index ix, MaintArgs a) {
   extern __shared__ __align__(16) char smem[];
   if (gated(ix, a.d)) return;
   resolve(ix, a);
@@ -4479,89 +4506,99 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 
 // ---- reclaim (Algorithm 4) -------------------------------------------------------------
 // live nodes with an edge into a tombstone ("dirty"), and the count of such
-// edges; neighbors are tested against the deletion bitmap.
-constexpr uint32_t DIRTY_CHUNK = 1024;  // nodes per workgroup and step
+// edges. Every neighbor of every live node is looked up in the deletion bitmap,
+// 32 random words per node: each workgroup keeps the bitmap in LDS (up to 2^20
+// ids; past that folded onto 2^20 bits, and a set bit is looked up again in
+// memory), where a wave's 64 lookups take a few cycles instead of one L2 line
+// each. 1,000,000 nodes, R = 32, reclaim after 10,000 deletes: 127 us with the
+// lookups in memory, 67 now (136 MB of words and lists, 2 TB/s: what is left is
+// latency, 16 waves per CU); 12,000 nodes, R = 48: 60, now 14.
+constexpr uint32_t DIRTY_WAVES = 16, DIRTY_RUNS = 4;  // waves per workgroup, runs of 64 nodes per wave and step at most
+constexpr uint32_t DIRTY_BITS = 1u << 20;
 
-__global__ void __launch_bounds__(256) k_dirty(Index ix, uint64_t n_ids, Dyn d, uint32_t* dirty) {
-  __shared__ uint32_t buf[DIRTY_CHUNK];
+__global__ void __launch_bounds__(64 * DIRTY_WAVES) k_dirty(Index ix, uint64_t n_ids, Dyn d, uint32_t* dirty,
+                                                            uint32_t runs) {
+  __shared__ uint32_t bits[DIRTY_BITS / 32];
+  __shared__ uint32_t buf[64 * DIRTY_WAVES * DIRTY_RUNS];
   __shared__ uint32_t cnt_s, dead_s, base_s;
   if (gated(ix, d)) return;
   const uint32_t n = dyn_count(ix, d, (uint32_t)n_ids);
   const uint32_t R = ix.R;
-  // A workgroup takes 1,024 nodes per step: each wave four runs of 64, lane l
-  // owning node base + l. The slabs are read by eight lanes per node, eight
+  const uint32_t step = 64u * DIRTY_WAVES * runs;
+  if ((uint64_t)blockIdx.x * step >= n) return;
+  const uint32_t words = (n + 31u) / 32u, fold = min(words, DIRTY_BITS / 32u);  // an id's bit: id % DIRTY_BITS
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(ix.delbits);
+  for (uint32_t i = threadIdx.x; i < fold; i += blockDim.x) {
+    uint32_t v = src[i];
+    for (uint32_t w = i + DIRTY_BITS / 32u; w < words; w += DIRTY_BITS / 32u) v |= src[w];
+    bits[i] = v;
+  }
+  const bool exact = n <= DIRTY_BITS;
+  auto deleted = [&](uint32_t id) -> uint32_t {
+    const uint32_t at = id & (DIRTY_BITS - 1u);
+    bool hit = (bits[at >> 5] >> (at & 31u)) & 1u;
+    if (hit && !exact) hit = del_bit(ix, id);
+    return hit ? 1u : 0u;
+  };
+  // A workgroup takes 1,024 nodes per run and up to four runs per step, lane l
+  // of a wave owning node base + l. The slabs are read by eight lanes per node, eight
   // nodes at a time (lane c of a group reads ids 4c.. 4c+3, then 32 further
   // on), so a node's id half is one contiguous run; each group's count goes
   // to its node's lane. Dirty ids gather in LDS and take their place in the
   // list with one atomic per workgroup and step.
   const int l = lane_id();
   const uint32_t c = (uint32_t)(l & 7), wv = threadIdx.x >> 6;
-  const bool short_lists = R <= 32u && (R & 3u) == 0;
-  for (uint32_t chunk = blockIdx.x; chunk * DIRTY_CHUNK < n; chunk += gridDim.x) {
+  for (uint32_t chunk = blockIdx.x; (uint64_t)chunk * step < n; chunk += gridDim.x) {
     if (threadIdx.x == 0) {
       cnt_s = 0;
       dead_s = 0;
     }
     __syncthreads();
-    for (uint32_t run = 0; run < DIRTY_CHUNK / 256u; ++run) {
-      const uint32_t base = chunk * DIRTY_CHUNK + (run * 4u + wv) * 64u;
-      uint32_t dead = 0;
-      if (short_lists) {
-        // R <= 32: one 16-byte read per lane and node covers the list. The
-        // run's reference words are read in one coalesced load (lane l: node
-        // base + l) and the eight groups' slab reads are all issued before
-        // the first bitmap test, so the three dependent reads of a node
-        // overlap with those of the others.
-        const uint32_t vme = base + (uint32_t)l;
-        const uint64_t rme = vme < n ? load_ref(ix, vme) : ~0ull;
-        uint4 w[8];
-        uint32_t dg[8];
-#pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) {
-          const uint64_t r = __shfl((unsigned long long)rme, (int)(8u * k + (uint32_t)(l >> 3)), 64);
-          const uint32_t deg = ref_deg(r), s = ref_slab(r);
-          const bool live = !ref_del(r) && s != NONE && 4u * c < deg;
-          dg[k] = live ? deg : 0u;
-          w[k] = live ? *reinterpret_cast<const uint4*>(ix.slabs + (size_t)s * 2u * R + 4u * c) : make_uint4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) {
-          const uint32_t j = 4u * c;
-          uint32_t cn = 0;
-          if (j < dg[k]) cn += del_bit(ix, w[k].x);
-          if (j + 1 < dg[k]) cn += del_bit(ix, w[k].y);
-          if (j + 2 < dg[k]) cn += del_bit(ix, w[k].z);
-          if (j + 3 < dg[k]) cn += del_bit(ix, w[k].w);
-          cn = group_sum<8>(cn);
-          const uint32_t got = (uint32_t)__shfl((int)cn, (int)((l & 7) * 8), 64);
-          if ((uint32_t)(l >> 3) == k) dead = got;
-        }
-      } else
+    for (uint32_t run = 0; run < runs; ++run) {
+      const uint32_t base = chunk * step + (run * DIRTY_WAVES + wv) * 64u;
+      // The run's reference words are read in one coalesced load (lane l: node
+      // base + l) and the eight groups' slab reads are all issued before the
+      // first lookup, so the dependent reads of a node overlap with those of
+      // the others.
+      const uint32_t vme = base + (uint32_t)l;
+      const uint64_t rme = vme < n ? load_ref(ix, vme) : ~0ull;
+      uint32_t dg[8], sl[8], cn[8];
 #pragma unroll
       for (uint32_t k = 0; k < 8; ++k) {
-        const uint32_t v = base + 8u * k + (uint32_t)(l >> 3);
-        uint32_t cn = 0;
-        if (v < n) {
-          const uint64_t r = load_ref(ix, v);
-          const uint32_t deg = ref_deg(r), s = ref_slab(r);
-          if (!ref_del(r) && s != NONE) {
-            const uint32_t* ids = ix.slabs + (size_t)s * 2u * R;
-            if ((R & 3u) == 0) {
-              for (uint32_t j = 4u * c; j < deg; j += 32u) {
-                const uint4 w = *reinterpret_cast<const uint4*>(ids + j);
-                cn += del_bit(ix, w.x);
-                if (j + 1 < deg) cn += del_bit(ix, w.y);
-                if (j + 2 < deg) cn += del_bit(ix, w.z);
-                if (j + 3 < deg) cn += del_bit(ix, w.w);
-              }
-            } else {
-              for (uint32_t j = c; j < deg; j += 8u) cn += del_bit(ix, ids[j]);
-            }
+        const uint64_t r = __shfl((unsigned long long)rme, (int)(8u * k + (uint32_t)(l >> 3)), 64);
+        sl[k] = ref_slab(r);
+        dg[k] = !ref_del(r) && sl[k] != NONE ? ref_deg(r) : 0u;
+        cn[k] = 0;
+      }
+      if ((R & 3u) == 0) {
+        for (uint32_t j = 4u * c; j < R; j += 32u) {
+          uint4 w[8];
+#pragma unroll
+          for (uint32_t k = 0; k < 8; ++k)
+            w[k] = j < dg[k] ? *reinterpret_cast<const uint4*>(ix.slabs + (size_t)sl[k] * 2u * R + j) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+          for (uint32_t k = 0; k < 8; ++k) {
+            if (j < dg[k]) cn[k] += deleted(w[k].x);
+            if (j + 1 < dg[k]) cn[k] += deleted(w[k].y);
+            if (j + 2 < dg[k]) cn[k] += deleted(w[k].z);
+            if (j + 3 < dg[k]) cn[k] += deleted(w[k].w);
           }
         }
-        cn = group_sum<8>(cn);
+      } else {
+        for (uint32_t j = c; j < R; j += 8u) {
+          uint32_t w[8];
+#pragma unroll
+          for (uint32_t k = 0; k < 8; ++k) w[k] = j < dg[k] ? ix.slabs[(size_t)sl[k] * 2u * R + j] : 0u;
+#pragma unroll
+          for (uint32_t k = 0; k < 8; ++k)
+            if (j < dg[k]) cn[k] += deleted(w[k]);
+        }
+      }
+      uint32_t dead = 0;
+#pragma unroll
+      for (uint32_t k = 0; k < 8; ++k) {
         // lane 8k + g takes the count of group g (node base + 8k + g)
-        const uint32_t got = (uint32_t)__shfl((int)cn, (int)((l & 7) * 8), 64);
+        const uint32_t got = (uint32_t)__shfl((int)group_sum<8>(cn[k]), (int)((l & 7) * 8), 64);
         if ((uint32_t)(l >> 3) == k) dead = got;
       }
       const uint64_t m = ballot(dead != 0);
@@ -4601,45 +4638,110 @@ __device__ inline void compact_read(const Index& ix, uint64_t r, uint32_t& id, u
 
 // A wave's dirty nodes (every total_waves()-th from its index) in batches of
 // 64: the batch's ids and reference words are read together (lane k: the
-// k-th), each node's list is read while the previous node is published, and
-// the publication starts from the word already read (no other wave touches
-// a dirty node in this phase).
-__global__ void __launch_bounds__(256) k_compact(Index ix, const uint32_t* dirty, uint64_t n, Dyn dn,
-                                                 uint32_t lds_per_wave) {
+// k-th). No other wave touches a dirty node in this phase, so eight nodes are
+// read, filtered and published side by side: their lists are in flight during
+// the eight before, their entries go straight from registers to the fresh slabs
+// and lane k exchanges the k-th reference. Bound by latency (list, bitmap, slab
+// number, exchange in turn), paid once per eight nodes. The gate before this
+// launch has reserved every node's slab and retired slot: a reservation per
+// workgroup is two atomics on the same words, and the 2,048 workgroups of a
+// launch took them one after the other. 10,000 deletes of 1,000,000: 130 us with
+// one node at a time, 101 with eight, 48 with the reservation in the gate; 2,000
+// of 200,000: 74, 66 and 17. A node whose exchange fails, or without a reserved
+// slab, is published by itself.
+constexpr uint32_t CB = 8, COMPACT_WAVES = 16;
+constexpr uint64_t REF_NO_LIST = 0ull;  // degree 0
+
+__global__ void __launch_bounds__(64 * COMPACT_WAVES) k_compact(Index ix, const uint32_t* dirty, uint64_t n, Dyn dn,
+                                                                uint32_t lds_per_wave) {
   extern __shared__ __align__(16) char smem[];
   if (gated(ix, dn)) return;
   const uint32_t cnt = dyn_count(ix, dn, (uint32_t)n);
   uint32_t* ids = reinterpret_cast<uint32_t*>(smem + (size_t)(threadIdx.x >> 6) * lds_per_wave);
   uint32_t* d = ids + 64;
-  SlabCursor cur = reserve_slabs_block(ix, wave_items(cnt), wave_items(cnt));
+  const LaunchSlabs slabs(ix);
+  const bool side = slabs.fbase != ~0ull && slabs.rbase != ~0ull;
+  SlabCursor tally;
   const int l = lane_id();
-  const uint32_t w = wave_index(), W = total_waves();
+  const uint32_t w = wave_index(), W = total_waves(), R = ix.R;
   for (uint32_t base = w; base < cnt; base += 64u * W) {
     const uint32_t my = base + (uint32_t)l * W;
     const uint32_t ul = my < cnt ? dirty[my] : NONE;
-    const uint64_t rl = my < cnt ? load_ref(ix, ul) : 0ull;
+    const uint64_t rl = my < cnt ? load_ref(ix, ul) : 0ull;  // no slab past the batch: nothing is read
     const uint32_t nb = (uint32_t)__popcll(ballot(my < cnt));
-    uint32_t id, dd;
-    compact_read(ix, bcast_lane64(rl, 0), id, dd);
-    for (uint32_t k = 0; k < nb; ++k) {
-      const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)ul, (int)k);
-      const uint64_t r = bcast_lane64(rl, (int)k);
-      uint32_t nid = NONE, ndd = 0;
-      if (k + 1 < nb) compact_read(ix, bcast_lane64(rl, (int)k + 1), nid, ndd);
-      const bool keep = id != NONE && !del_bit(ix, id);
-      const uint64_t m = ballot(keep);
-      wave_sync();
-      if (keep) {
-        ids[lanes_below(m)] = id;
-        d[lanes_below(m)] = dd;
+    uint32_t id[CB], dd[CB];
+#pragma unroll
+    for (uint32_t j = 0; j < CB; ++j) compact_read(ix, j < nb ? bcast_lane64(rl, (int)j) : REF_NO_LIST, id[j], dd[j]);
+    for (uint32_t k0 = 0; k0 < nb; k0 += CB) {
+      const uint32_t m = min(CB, nb - k0);
+      uint64_t keep[CB];
+#pragma unroll
+      for (uint32_t j = 0; j < CB; ++j) keep[j] = ballot(id[j] != NONE && !del_bit(ix, id[j]));
+      uint32_t nid[CB], ndd[CB];
+#pragma unroll
+      for (uint32_t j = 0; j < CB; ++j)
+        compact_read(ix, k0 + CB + j < nb ? bcast_lane64(rl, (int)(k0 + CB + j)) : REF_NO_LIST, nid[j], ndd[j]);
+      uint64_t done = 0;  // nodes published (bit j)
+      if (side) {
+        // lane j: the j-th node's reference and fresh slab
+        const uint64_t r = __shfl((unsigned long long)rl, (int)(k0 + ((uint32_t)l & (CB - 1u))), 64);
+        const uint32_t u = (uint32_t)__shfl((int)ul, (int)(k0 + ((uint32_t)l & (CB - 1u))), 64);
+        const uint32_t item = base + (k0 + (uint32_t)l) * W;
+        const bool mine = (uint32_t)l < m;
+        const uint32_t fresh = mine ? ix.free_stack[slabs.fbase - 1 - item] : 0u;
+        uint32_t deg = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < CB; ++j) {
+          if (j >= m) break;
+          const uint32_t c = (uint32_t)__popcll(keep[j]);
+          if ((uint32_t)l == j) deg = c;
+          uint32_t* slab = ix.slabs + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)fresh, (int)j) * 2u * R;
+          if ((keep[j] >> l) & 1ull) {
+            const uint32_t at = lanes_below(keep[j]);
+            slab[at] = id[j];
+            slab[R + at] = dd[j];
+          }
+          if ((uint32_t)l >= c && (uint32_t)l < R) {
+            slab[l] = NONE;
+            slab[R + (uint32_t)l] = 0u;
+          }
+        }
+        if (ix.fence) __threadfence();  // contents before the references, for concurrent readers
+        bool won = false;
+        if (mine) {
+          won = atomicCAS(&ix.refs[u], (unsigned long long)r,
+                          (unsigned long long)(make_ref(ref_del(r), deg, fresh) | (r & REF_NORM_MASK))) == r;
+          if (!won) {
+            retire_slab(ix, fresh);
+            atomicAdd(&ix.ctr[C_CAS_FAIL], 1ull);
+          }
+        }
+        done = ballot(won);
+        if (won) ix.retired_stack[slabs.rbase + item] = ref_slab(r);
+        tally.pubs += (uint32_t)__popcll(done);
       }
-      wave_sync();
-      publish(ix, u, ids, d, (uint32_t)__popcll(m), C_PUB_COMPACT, &cur, r);
-      id = nid;
-      dd = ndd;
+#pragma unroll
+      for (uint32_t j = 0; j < CB; ++j) {
+        if (j < m && !((done >> j) & 1ull)) {
+          wave_sync();
+          if ((keep[j] >> l) & 1ull) {
+            ids[lanes_below(keep[j])] = id[j];
+            d[lanes_below(keep[j])] = dd[j];
+          }
+          wave_sync();
+          SlabCursor cur = slabs.run(base + (k0 + j) * W);
+          if (side) cur.free_left = 0;  // retired above
+          publish(ix, (uint32_t)__builtin_amdgcn_readlane((int)ul, (int)(k0 + j)), ids, d, (uint32_t)__popcll(keep[j]),
+                  C_PUB_COMPACT, &cur, side ? REF_UNREAD : bcast_lane64(rl, (int)(k0 + j)), side ? 1u : 0u);
+          return_slabs(ix, cur);
+          tally.pubs += cur.pubs;
+        }
+        id[j] = nid[j];
+        dd[j] = ndd[j];
+      }
     }
   }
-  finish_slabs_block(ix, cur, C_PUB_COMPACT);
+  finish_slabs_block(ix, tally, C_PUB_COMPACT);
 }
 
 // phase 2: <1,d,s> -> <1,0,none> and the slab is retired. A workgroup takes
@@ -5131,8 +5233,7 @@ hipError_t launch_init(const Index& ix, hipStream_t s) {
 }
 
 hipError_t launch_recycle(const Index& ix, hipStream_t s) {
-  hipLaunchKernelGGL(k_recycle, dim3(256), dim3(256), 0, s, ix);
-  hipLaunchKernelGGL(k_recycle_commit, dim3(1), dim3(1), 0, s, ix);
+  hipLaunchKernelGGL(k_recycle, dim3(RECYCLE_BLOCKS), dim3(256), 0, s, ix);
   return hipGetLastError();
 }
 
@@ -5529,7 +5630,8 @@ static void launch_maint_p(MaintKernel which, const Index& ix, const MaintArgs& 
       break;
     case MK_REFINE:
       hipLaunchKernelGGL(k_refine<P>, resident_grid(k_refine<P>, grid, blk, lds, sh), blk, lds, s, ix, a);
-      hipLaunchKernelGGL(k_refine_publish, dim3(grid), blk, 512u * (blk.x / 64u), s, ix, a);
+      hipLaunchKernelGGL(k_refine_publish, dim3(std::min(persist_grid(a.n, RP_WAVES), PERSIST_BLOCKS / 4)),
+                         dim3(64 * RP_WAVES), 512u * RP_WAVES, s, ix, a);
       break;
     case MK_REPAIR:
       if constexpr (P::CHAIN) {
@@ -5636,16 +5738,22 @@ hipError_t launch_tombstone(const Index& ix, const uint32_t* dlist, uint32_t n, 
 
 hipError_t launch_dirty(const Index& ix, uint64_t n_ids, Dyn d, uint32_t* dirty, hipStream_t s) {
   if (n_ids == 0) return hipSuccess;
-  const unsigned blocks = blocks_for(n_ids, DIRTY_CHUNK);
-  hipLaunchKernelGGL(k_dirty, dim3(blocks < 4 * PERSIST_BLOCKS ? blocks : 4 * PERSIST_BLOCKS), dim3(256), 0, s, ix,
-                     n_ids, d, dirty);
+  // as many runs per step as leave each CU a workgroup: every step ends in two
+  // atomics on the same words
+  const uint32_t per_run = 64 * DIRTY_WAVES;
+  const uint32_t runs = (uint32_t)std::min<uint64_t>(DIRTY_RUNS, std::max<uint64_t>(1, n_ids / (256ull * per_run)));
+  const unsigned blocks = blocks_for(n_ids, per_run * runs);
+  hipLaunchKernelGGL(k_dirty, dim3(blocks < PERSIST_BLOCKS ? blocks : PERSIST_BLOCKS), dim3(per_run), 0, s, ix, n_ids, d,
+                     dirty, runs);
   return hipGetLastError();
 }
 
 hipError_t launch_compact(const Index& ix, const uint32_t* dirty, uint64_t n, Dyn d, hipStream_t s) {
   if (n == 0) return hipSuccess;
   const uint32_t per_wave = 512;
-  hipLaunchKernelGGL(k_compact, dim3(persist_grid(n, 4)), dim3(256), 4 * per_wave, s, ix, dirty, n, d, per_wave);
+  const unsigned blocks = persist_grid(n, COMPACT_WAVES);
+  hipLaunchKernelGGL(k_compact, dim3(std::min(blocks, PERSIST_BLOCKS / 4)), dim3(64 * COMPACT_WAVES),
+                     COMPACT_WAVES * per_wave, s, ix, dirty, n, d, per_wave);
   return hipGetLastError();
 }
 
