@@ -275,11 +275,12 @@ __global__ void __launch_bounds__(1024) k_refresh_entries(Index ix, uint32_t nex
 // ---- start-set scoring: the L best start nodes of every query --------------------------
 // The start set (the entry set, or the batch itself for a bootstrap) is the
 // same for every query of a launch, so scoring it is one dense block of
-// distances. Float rows: k_scan_dist_f (64 queries x 256 start rows per
-// workgroup, staged through LDS) writes the distance matrix and k_scan_select
-// takes, with one wave per query, the exact L smallest (distance, id) keys.
-// Uint8 rows are scored on the matrix cores twice instead (first for bounds,
-// then for the few keys under them), so the matrix never reaches memory.
+// distances. Float rows: k_scan_dist_f (tiles staged through LDS) writes the
+// distance matrix, and k_scan_pick (k_scan_select past SCAN_FILTER_L_MAX) takes,
+// with one wave per query, the exact L smallest (distance, id) keys. Uint8 rows
+// with few query-row pairs or long lists do the same on the matrix cores;
+// otherwise they are scored twice instead (first for bounds, then for the few
+// keys under them), so the matrix never reaches memory.
 // Start rows are in ascending id order, so the row index breaks distance ties
 // exactly as the id does.
 constexpr int SD_E = 256;  // float start rows: group slots come in blocks of this many rows
@@ -985,9 +986,9 @@ __global__ void __launch_bounds__(256) k_scan_select(Index ix, ScanArgs a, uint3
 }
 
 // uint8 rows with many query-row pairs, in four launches that never write the
-// distance matrix: group
-// minima (k_scan_dist<SCAN_MIN>), each query's bound (k_scan_bound), the keys
-// at or below it (k_scan_dist<SCAN_FILTER>), and their sort (k_scan_final).
+// distance matrix: group minima (k_scan_dist<SCAN_MIN>), each query's bound
+// (k_scan_bound), the keys at or below it (k_scan_dist<SCAN_FILTER>), and their
+// sort (k_scan_final).
 // A query whose keys overflow its list (heavy ties at the bound) has its
 // distance row written out and takes the general selection above.
 __global__ void __launch_bounds__(256) k_scan_bound(Index ix, ScanArgs a) {
@@ -3969,7 +3970,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 // neighbor, two thirds of the SIMD cycles) and the reads that lead to the rows;
 // 4 waves per SIMD (5 spill: 2.87 -> 3.02 ms per pass). 10,000 deletes and
 // 10,000 inserts at 1M rows, with the general kernels' remainder: repair 2.05 ->
-// 0.70 ms, reverse edges 1.14 -> 0.30 (2,000 and 2,000 at 200k: 0.52 -> 0.22,
+// 0.65 ms, reverse edges 1.14 -> 0.29 (2,000 and 2,000 at 200k: 0.52 -> 0.21,
 // 0.28 -> 0.09).
 struct CoverLds {
   uint32_t* id;    // [64] the current target's ids by slot (one of bid's rows)
