@@ -5777,9 +5777,10 @@ hipError_t launch_export(const Index& ix, uint64_t n_ids, uint32_t* nbr, uint32_
 uint64_t bruteforce_norm_bytes(uint64_t n_ids) { return (n_ids * 4 + 255) / 256 * 256; }
 
 // float rows: queries per launch pair, so that their group minima fit the scratch
+// and the grids (few rows, many queries) stay below 2^32 threads
 static uint32_t bruteforce_f32_chunk(uint32_t nq, uint64_t n_ids) {
   const uint64_t per = (n_ids + 63) / 64 * 4;
-  return (uint32_t)std::min<uint64_t>(nq, std::max<uint64_t>(1, BF_SCRATCH_MAX / std::max<uint64_t>(1, per)));
+  return (uint32_t)std::min<uint64_t>(std::min(nq, 8u << 20), std::max<uint64_t>(1, BF_SCRATCH_MAX / std::max<uint64_t>(1, per)));
 }
 
 uint64_t bruteforce_scratch_bytes(const Index& ix, uint32_t nq, uint64_t n_ids) {
