@@ -105,18 +105,13 @@ struct TravF {
     float v[CPL][EPC];
   };
 
-  // FP8: the query is held at 1/256 of its size, so that the products of the
-  // codes' own values are those of the codes' values / 256
   __device__ static Q load_query(const float* q) {
     Q r;
     const int c = lane_id() % G;
 #pragma unroll
     for (int t = 0; t < CPL; ++t)
 #pragma unroll
-      for (int e = 0; e < EPC; ++e) {
-        const float x = q[(size_t)(t * G + c) * EPC + e];
-        r.v[t][e] = TRAV == TRAV_FP8 ? x * 0x1p-8f : x;
-      }
+      for (int e = 0; e < EPC; ++e) r.v[t][e] = q[(size_t)(t * G + c) * EPC + e];
     return r;
   }
 
@@ -127,8 +122,10 @@ struct TravF {
   }
 
   // this lane's share of <q, row> (FP8: of <q, row/scale>/256). FP8 codes are
-  // converted two at a time by the hardware, which reads 0x7F and 0xFF as NaN:
-  // EXACT_CODES decodes them by their bit pattern (to +-480) instead
+  // converted two at a time by the hardware, 1/256 with them (the query holds
+  // every bit it came with: components below 2^-118 would lose some at 1/256),
+  // which reads 0x7F and 0xFF as NaN: EXACT_CODES decodes them by their bit
+  // pattern (to +-480) instead
   template <bool EXACT_CODES = false>
   __device__ static float partial(const Q& q, const uint4 (&w)[CPL]) {
     float acc = 0.f;
@@ -149,12 +146,12 @@ struct TravF {
         for (int e = 0; e < 4; ++e)
 #pragma unroll
           for (int b = 0; b < 4; ++b)
-            acc = __builtin_fmaf(q.v[t][4 * e + b], 256.0f * e4m3_div256((wd[e] >> (8 * b)) & 0xFFu), acc);
+            acc = __builtin_fmaf(q.v[t][4 * e + b], e4m3_div256((wd[e] >> (8 * b)) & 0xFFu), acc);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)wd[e], false);
-          const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)wd[e], true);
+          const auto lo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(wd[e], 0x1p-8f, false);
+          const auto hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(wd[e], 0x1p-8f, true);
           acc = __builtin_fmaf(q.v[t][4 * e], lo[0], acc);
           acc = __builtin_fmaf(q.v[t][4 * e + 1], lo[1], acc);
           acc = __builtin_fmaf(q.v[t][4 * e + 2], hi[0], acc);
