@@ -218,22 +218,29 @@ struct TravF {
           if (c == u) dot = d;
         }
       }
-      if constexpr (TRAV == TRAV_FP8) {
-        if (ballot(mine && dot != dot)) {  // a NaN code (or a NaN query): decoded by bit pattern
-#pragma unroll 1
-          for (int u = 0; u < used; ++u) {
-            const int vi = base + u * VPP + grp;
-            uint4 x[CPL];
-#pragma unroll
-            for (int t = 0; t < CPL; ++t) x[t] = vi < cnt ? row(ix, ids[vi])[t * G + c] : make_uint4(0, 0, 0, 0);
-            const float d = group_sum_t<G, float>(partial<true>(q, x));
-            if ((U == 8 ? (l & 7) : c) == u) dot = d;
-          }
-        }
-      }
+      const uint64_t nan = ballot(mine && dot != dot);
       if (mine) {
         ck[my] = make_key(fkey(1.0f - sc * dot), id);
         if (cr) cr[my] = r;
+      }
+      // A NaN: from a NaN code, which FP8 decodes by bit pattern, or from the
+      // vectors, and then its sign (by which it sorts first or last) hangs on
+      // the order of the sum. Both are settled a row at a time, as lane 0 of
+      // the row's group sums it. (The lane's number is read again: kept for this
+      // it takes a register of the sum's, and some searches a wave per SIMD.)
+      if (__builtin_expect(nan != 0, 0)) {
+        int ln;
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+        const int cl = ln % G;
+#pragma unroll 1
+        for (int u = 0; u < used; ++u) {
+          const int vi = base + u * VPP + ln / G;
+          uint4 x[CPL];
+#pragma unroll
+          for (int t = 0; t < CPL; ++t) x[t] = vi < cnt ? row(ix, ids[vi])[t * G + cl] : make_uint4(0, 0, 0, 0);
+          const float d = group_sum_t<G, float>(partial<TRAV == TRAV_FP8>(q, x));
+          if (cl == 0 && vi < cnt) ck[vi] = make_key(fkey(1.0f - scale(ix, ids[vi]) * d), ids[vi]);
+        }
       }
     }
   }
@@ -323,7 +330,19 @@ __device__ inline int robust_prune_f32(const Index& ix, uint32_t p, const uint32
       for (int u = 0; u < 8; ++u) v[u] = RF::part(pf, xf[u]);
       const float dot = group_sum8<G>(v);
       const int vi = base + i8 * VPP + grp;
-      if ((l % G) < 8 && vi < n && s.keys[vi] != KEY_NONE) s.keys[vi] = make_key(fkey(1.0f - dot), cand[vi]);
+      const bool mine = (l % G) < 8 && vi < n && s.keys[vi] != KEY_NONE;
+      const uint64_t nan = ballot(mine && dot != dot);
+      if (mine) s.keys[vi] = make_key(fkey(1.0f - dot), cand[vi]);
+      if (__builtin_expect(nan != 0, 0)) {  // a NaN's sign: as lane 0 of the row's group sums it
+#pragma unroll 1
+        for (int u = 0; u < 8; ++u) {
+          const int vu = base + u * VPP + grp;
+          const bool in = vu < n && s.keys[vu] != KEY_NONE;
+          if (in) RF::load(ix, cand[vu], xf[0]);
+          const float d = RF::dotp(pf, xf[0]);
+          if (in && l % G == 0) s.keys[vu] = make_key(fkey(1.0f - d), cand[vu]);
+        }
+      }
     }
     wave_sync();
   }

@@ -5090,7 +5090,9 @@ __global__ void __launch_bounds__(64) k_bruteforce_f32(Index ix, const float* q,
 //                 at or below the bound (a dozen or so) again, for their keys.
 // Both add a row's products in the order of the distance batches (lane c of G:
 // the chunks c, G + c, 2G + c in turn, then the lanes in pairs), so distances,
-// bounds and results keep its bits. The first pass is bound by FP32 issue (one
+// bounds and results keep its bits, but for a NaN's sign, which decides whether
+// it sorts first or last: the first pass writes a NaN as -infinity, and a group
+// with such a minimum is always scored again and bounds nothing. The first pass is bound by FP32 issue (one
 // FMA per lane and element): a lane keeps 96 elements of its row in registers
 // and the query's come as scalars, so nothing but the FMAs is left in the loop;
 // sums that wait for their pair (rows past 96 elements) and the keys, which are
@@ -5102,6 +5104,7 @@ constexpr int BF_WAVES = 4;                        // groups per workgroup, all 
 template <int G> constexpr int bf_queries() { return G <= 16 ? 32 : 16; }  // and how many of those
 template <int G> constexpr int bf_levels() { return G <= 16 ? 1 : G == 32 ? 2 : 3; }  // log2(G / 8) waiting sums
 constexpr int BF_ROW = 68;                         // words per query in LDS: 64 lanes, padded for 16-byte reads
+constexpr uint32_t BF_ANY = 0x007FFFFFu;           // key of -infinity: a group that may hold a NaN
 constexpr uint64_t BF_SCRATCH_MAX = 256ull << 20;  // group minima per launch; more queries take further launches
 
 template <int G>
@@ -5159,7 +5162,7 @@ __global__ void __launch_bounds__(64 * BF_WAVES) k_bf_min_f32(Index ix, const fl
       int lv = 0;
       for (; (b >> lv) & 1; ++lv) s = __builtin_bit_cast(float, part[lv][i][l]) + s;
       if (b + 1 < G / 8) part[lv][i][l] = __builtin_bit_cast(uint32_t, s);
-      else part[0][i][l] = live ? fkey(1.0f - s) : D_INVALID;
+      else part[0][i][l] = live ? fkey(__builtin_fmaxf(1.0f - s, -INFINITY)) : D_INVALID;
     }
   }
   wave_sync();
@@ -5185,7 +5188,10 @@ __global__ void __launch_bounds__(64) k_bf_near_f32(Index ix, const float* q, ui
   const uint32_t* gm = gmin + (size_t)qi * n_grp;
   // the k-th smallest of the 64 lanes' smallest minima: k groups lie at or below it
   uint32_t bound = D_INVALID;
-  for (uint32_t i = (uint32_t)l; i < n_grp; i += 64) bound = min(bound, gm[i]);
+  for (uint32_t i = (uint32_t)l; i < n_grp; i += 64) {
+    const uint32_t m = gm[i];
+    bound = m <= BF_ANY ? bound : min(bound, m);
+  }
   wave_sort32(bound);
   bound = (uint32_t)__builtin_amdgcn_readlane((int)bound, (int)k - 1);
   uint64_t best[1] = {KEY_NONE};  // the 64 smallest keys so far, ascending

@@ -33,3 +33,55 @@ def test_fp8_queries_near_the_smallest_normal(dim):
         g.close()
     assert np.array_equal(found[0][0], found[1][0])
     assert np.array_equal(found[0][1], found[1][1])
+
+
+def _strange(rng, n, dim):
+    """Unit rows; in two fifths of them one component, in a few of them all, an infinity or a NaN of either sign."""
+    x = rng.standard_normal((n, dim)).astype(np.float32)
+    x /= np.linalg.norm(x, axis=1, keepdims=True)
+    odd = np.array([0x7F800000, 0xFF800000, 0x7FC00000, 0xFFC00000], np.uint32).view(np.float32)
+    for i in np.flatnonzero(rng.random(n) < 0.4):
+        x[i, rng.integers(0, dim, rng.integers(1, 3))] = odd[rng.integers(0, 4)]
+    for j, i in enumerate(rng.choice(n, 8, replace=False)):
+        x[i] = odd[j % 4]
+    return x
+
+
+def _distances(x, q):
+    """q's distances to each row of x as the brute force gives them when that row is among sixteen live ones."""
+    from paper_2607_02543_amd import etale
+    g = etale.Index(x.shape[1], R=4, L_build=8, n_entry=16, id_capacity=x.shape[0], slab_capacity=4000, max_batch=16,
+                    metric=etale.METRIC_IP_F32)
+    out = np.empty((q.shape[0], x.shape[0]), np.uint32)
+    for b in range(0, x.shape[0], 16):
+        at = g.insert(_up(x[b:b + 16]))
+        i, d = g.bruteforce(_up(q), at.numel())
+        i, d = i.cpu().numpy(), d.cpu().numpy().view(np.uint32)
+        assert np.array_equal(np.sort(i, axis=1), np.tile(at.cpu().numpy(), (q.shape[0], 1)))
+        np.put_along_axis(out, i, d, axis=1)
+        g.delete(at)
+        g.reclaim()
+    g.close()
+    return out
+
+
+# the first pass's order of a sum need not be the second's where a NaN is in it: groups of 64 rows with and without one
+@pytest.mark.parametrize("dim", [96, 192, 384, 768])
+def test_infinities_and_nans_rank_by_the_rows_own_distance(dim):
+    from paper_2607_02543_amd import etale
+    rng = np.random.default_rng(dim + 1)
+    n = 960
+    x, q = _strange(rng, n, dim), _strange(rng, 50, dim)
+    x[320:640] = np.abs(np.nan_to_num(x[320:640], nan=0.0, posinf=0.0, neginf=0.0))
+    d = _distances(x, q)
+    g = etale.Index(dim, R=12, L_build=16, n_entry=100, id_capacity=n, slab_capacity=20_000, max_batch=240,
+                    metric=etale.METRIC_IP_F32)
+    for b in range(0, n, 240):
+        g.insert(_up(x[b:b + 240]))
+    i, got = g.bruteforce(_up(q), 16)
+    i, got = i.cpu().numpy(), got.cpu().numpy().view(np.uint32)
+    key = np.where(d >> 31, ~d, d | 0x80000000).astype(np.uint32)  # the order of binary32 values, NaNs at both ends
+    want = np.stack([np.lexsort((np.arange(n), r))[:16] for r in key])
+    assert np.array_equal(got, np.take_along_axis(d, want, axis=1))
+    assert np.array_equal(i, want)
+    g.close()
