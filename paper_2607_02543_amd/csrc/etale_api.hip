@@ -49,6 +49,7 @@ struct etale_index {
   uint32_t* rank = nullptr;       // grouping: a pair's arrival rank within its target,
   uint32_t* tlist = nullptr;      //   and the targets
   unsigned long long* dmark = nullptr;  // [id_capacity] delete marks
+  FarMarks far;                         // and those of ids past it
   uint32_t* tcnt = nullptr;             // [id_capacity] pairs per target while a list is grouped
   int32_t* status = nullptr;      // round status words of the calls that do not take one
   bool no_chain = false;          // reverse edges without the cached candidate state
@@ -503,8 +504,8 @@ etale_status enqueue_round(etale_index* ix, const RoundPlan& p) {
     Dyn dd;
     dd.skip = G_FAIL;
     dd.n_ctr = C_R_NDEL;
-    HIP_TRY(launch_del_mark(d, p.del_ids, p.max_d, dd, s));
-    HIP_TRY(launch_del_classify(d, p.del_ids, p.max_d, dd, p.del_status, ix->dlist, s));
+    HIP_TRY(launch_del_mark(d, ix->far, p.del_ids, p.max_d, dd, s));
+    HIP_TRY(launch_del_classify(d, ix->far, p.del_ids, p.max_d, dd, p.del_status, ix->dlist, s));
   }
   HIP_TRY(launch_round_gate(d, ix->cfg.tombstone_only, BOOT_MAX, p.status, s, p.reclaim));
   if (p.max_d) {
@@ -764,6 +765,11 @@ etale_status etale_create(const etale_config* cfg, etale_t* out) {
   ALLOC(ix->rank, B * R * 4);
   ALLOC(ix->tlist, B * R * 4);
   ALLOC(ix->dmark, C * 8);
+  uint64_t far = 64;  // at most half full, so that probes stay short
+  while (far < 2 * B) far <<= 1;
+  ALLOC(ix->far.id, far * 8);
+  ALLOC(ix->far.mark, far * 8);
+  ix->far.mask = (uint32_t)(far - 1);
   ALLOC(ix->tcnt, C * 4);
   ALLOC(ix->status, 16);
 #undef ALLOC
@@ -805,7 +811,8 @@ etale_status etale_create(const etale_config* cfg, etale_t* out) {
   d.tcnt = ix->tcnt;
   d.ent_x = ix->ent_x;
   d.ent_norm = ix->ent_norm;
-  if (launch_init(d, ix->stream) != hipSuccess || hipStreamSynchronize(ix->stream) != hipSuccess)
+  if (launch_init(d, ix->stream) != hipSuccess || launch_far_init(ix->far, ix->stream) != hipSuccess ||
+      hipStreamSynchronize(ix->stream) != hipSuccess)
     return cleanup(ETALE_EDEVICE, "init");
   if (noalloc_scratch_address(&ix->noalloc) != hipSuccess) return cleanup(ETALE_EDEVICE, "scratch symbol");
   *out = ix;

@@ -143,9 +143,18 @@ hipError_t launch_reverse_pairs(const Index& ix, const MaintArgs& a, hipStream_t
 hipError_t launch_group_reverse(const Index& ix, const MaintArgs& a, const GroupArgs& g, hipStream_t s);
 // the deleted nodes' live neighbors as pairs (a, u)
 hipError_t launch_group_repair(const Index& ix, const MaintArgs& a, const GroupArgs& g, hipStream_t s);
-hipError_t launch_del_mark(const Index& ix, const uint32_t* ids, uint32_t n, Dyn d, hipStream_t s);
-hipError_t launch_del_classify(const Index& ix, const uint32_t* ids, uint32_t n, Dyn d, uint8_t* status,
-                               uint32_t* dlist, hipStream_t s);
+// The delete marks of ids past the id space, hashed: the call and the id, and its
+// mark. (An argument of the two kernels that read them: in Index, every launch
+// would carry them, a tenth of a microsecond each.)
+struct FarMarks {
+  unsigned long long* id = nullptr;
+  unsigned long long* mark = nullptr;
+  uint32_t mask = 0;  // slots less one: a power of two of at least twice max_batch
+};
+hipError_t launch_far_init(const FarMarks& f, hipStream_t s);
+hipError_t launch_del_mark(const Index& ix, const FarMarks& f, const uint32_t* ids, uint32_t n, Dyn d, hipStream_t s);
+hipError_t launch_del_classify(const Index& ix, const FarMarks& f, const uint32_t* ids, uint32_t n, Dyn d,
+                               uint8_t* status, uint32_t* dlist, hipStream_t s);
 hipError_t launch_tombstone(const Index& ix, const uint32_t* dlist, uint32_t n, Dyn d, hipStream_t s);
 hipError_t launch_dirty(const Index& ix, uint64_t n_ids, Dyn d, uint32_t* dirty, hipStream_t s);
 hipError_t launch_compact(const Index& ix, const uint32_t* dirty, uint64_t n, Dyn d, hipStream_t s);
