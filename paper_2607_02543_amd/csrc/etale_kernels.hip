@@ -2454,21 +2454,110 @@ __global__ void __launch_bounds__(256) k_group_scatter(Index ix, GroupArgs g) {
   }
 }
 
-// each run in ascending source order (a lane per run up to four pairs, else the
-// wave), and the counters back to zero
+// a run of n <= ORDER_WAVE pairs in ascending source order, through
+// keys (the wave's own ORDER_WAVE words of LDS)
+constexpr uint32_t ORDER_WAVE = 512, ORDER_LDS = 4096;
+
+__device__ inline void order_run(uint64_t* run, uint32_t n, uint64_t* keys) {
+  const uint32_t l = (uint32_t)lane_id();
+  const uint32_t np = (uint32_t)next_pow2_ge64((int)n);
+  wave_sync();
+  for (uint32_t x = l; x < np; x += 64u) keys[x] = x < n ? run[x] : KEY_NONE;
+  wave_sync();
+  wave_bitonic_sort(keys, (int)np);
+  for (uint32_t x = l; x < n; x += 64u) run[x] = keys[x];
+}
+
+// Any longer run, by the workgroup: pieces of ORDER_LDS pairs sorted in LDS, then
+// merged two by two between the list and the raw one (free by now), every pair
+// to its place among its own piece's and the other's.
+__device__ inline void order_long_run(uint64_t* run, uint64_t* spare, uint32_t most, uint32_t* keys) {
+  const uint32_t tg = (uint32_t)(run[0] >> 32);
+  uint32_t n = 0;  // its length
+  for (;;) {
+    const uint32_t x = n + threadIdx.x;
+    const uint64_t key = x < most ? run[x] : KEY_NONE;
+    const uint32_t in = (uint32_t)__syncthreads_count(key != KEY_NONE && (uint32_t)(key >> 32) == tg);
+    n += in;
+    if (in < 256u) break;
+  }
+  for (uint32_t p = 0; p < n; p += ORDER_LDS) {
+    const uint32_t m = min(ORDER_LDS, n - p);
+    uint32_t np = 256;
+    while (np < m) np <<= 1;
+    for (uint32_t x = threadIdx.x; x < np; x += 256u) keys[x] = x < m ? (uint32_t)run[p + x] : NONE;
+    __syncthreads();
+    for (uint32_t k = 2; k <= np; k <<= 1)
+      for (uint32_t j = k >> 1; j; j >>= 1) {
+        for (uint32_t y = threadIdx.x; y < np / 2; y += 256u) {
+          const uint32_t x = ((y & ~(j - 1u)) << 1) | (y & (j - 1u));
+          const uint32_t a = keys[x], b = keys[x + j];
+          if ((a > b) == ((x & k) == 0)) {
+            keys[x] = b;
+            keys[x + j] = a;
+          }
+        }
+        __syncthreads();
+      }
+    for (uint32_t x = threadIdx.x; x < m; x += 256u) run[p + x] = pair_key(tg, keys[x]);
+    __syncthreads();
+  }
+  uint64_t *from = run, *to = spare;
+  for (uint64_t w = ORDER_LDS; w < n; w <<= 1) {
+    for (uint32_t x = threadIdx.x; x < n; x += 256u) {
+      const uint64_t key = from[x];
+      const uint32_t a0 = (uint32_t)(x / (2 * w) * (2 * w)), mid = (uint32_t)min<uint64_t>(a0 + w, n);
+      const bool left = x < mid;  // the other piece's pairs before this one
+      uint32_t lo = left ? mid : a0, hi = left ? (uint32_t)min<uint64_t>(a0 + 2 * w, n) : mid;
+      const uint32_t other = lo;
+      while (lo < hi) {
+        const uint32_t c = lo + ((hi - lo) >> 1);
+        if (left ? from[c] < key : from[c] <= key) lo = c + 1;
+        else hi = c;
+      }
+      to[a0 + (x - (left ? a0 : mid)) + (lo - other)] = key;
+    }
+    __syncthreads();
+    uint64_t* t = from;
+    from = to;
+    to = t;
+  }
+  if (from != run) {
+    for (uint32_t x = threadIdx.x; x < n; x += 256u) run[x] = from[x];
+    __syncthreads();
+  }
+}
+
+// Each run in ascending source order, and the counters back to zero: a lane per
+// run up to four pairs, a wave up to ORDER_WAVE, the workgroup past that. A wave
+// takes as few runs as leave every wave some: while an index is small most of its
+// nodes get dozens of offers from a batch, each run a microsecond of one wave.
+// Against 64 runs per wave, and past 64 pairs each source ranked against every
+// other: 8.2 -> 2.0 ms over the 1M build, its longest launch 1,780 -> 95 us; an
+// insert of 16,384 rows that all go to one node 321 -> 38 ms, now the offers' own
+// work. Bound by latency where runs are short (10,000 deletes or inserts at 1M:
+// 13 us either way).
 __global__ void __launch_bounds__(256) k_group_order(Index ix, GroupArgs g) {
+  __shared__ __align__(16) uint32_t keys[ORDER_LDS];
+  __shared__ uint32_t long_at[256], long_n;
   if (gated(ix, g.d)) return;
   const uint32_t nseg = (uint32_t)ix.ctr[g.seg_ctr], np = (uint32_t)ix.ctr[g.pair_ctr];
   const uint32_t l = (uint32_t)lane_id();
-  for (uint32_t c0 = blockIdx.x * 256u + (threadIdx.x & ~63u); c0 < nseg; c0 += gridDim.x * 256u) {
-    const uint32_t i = c0 + l;
-    const uint32_t at = i < nseg ? g.seg[i] : 0u, target = i < nseg ? g.tlist[i] : NONE;
-    if (i < nseg) ix.tcnt[target] = 0;
+  uint64_t* const mine_keys = reinterpret_cast<uint64_t*>(keys) + (threadIdx.x >> 6) * ORDER_WAVE;
+  // runs per wave (not exact: the loop takes what is left)
+  const uint32_t per = min(64u, (uint32_t)((float)nseg * __builtin_amdgcn_rcpf((float)total_waves())) + 1u);
+  for (uint32_t c0 = blockIdx.x * 4u * per; c0 < nseg; c0 += gridDim.x * 4u * per) {
+    if (threadIdx.x == 0) long_n = 0;
+    __syncthreads();
+    const uint32_t i = c0 + (threadIdx.x >> 6) * per + l;
+    const bool mine = l < per && i < nseg;
+    const uint32_t at = mine ? g.seg[i] : 0u, target = mine ? g.tlist[i] : NONE;
+    if (mine) ix.tcnt[target] = 0;
     uint32_t s[4], len = 0;
-    bool more = i < nseg;
+    bool more = mine;
 #pragma unroll
     for (uint32_t k = 0; k < 5; ++k) {
-      const uint64_t key = i < nseg && at + k < np ? g.out[at + k] : KEY_NONE;
+      const uint64_t key = mine && at + k < np ? g.out[at + k] : KEY_NONE;
       more = more && (uint32_t)(key >> 32) == target && key != KEY_NONE;
       if (k < 4) s[k] = more ? (uint32_t)key : NONE;
       len += more && k < 4 ? 1u : 0u;
@@ -2492,7 +2581,7 @@ __global__ void __launch_bounds__(256) k_group_order(Index ix, GroupArgs g) {
       const int e = (int)__builtin_ctzll(m);
       const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)at, e), tg = (uint32_t)__builtin_amdgcn_readlane((int)target, e);
       uint32_t n = 0;  // the run's length
-      for (;;) {
+      while (n <= ORDER_WAVE) {
         const uint64_t key = b + n + l < np ? g.out[b + n + l] : KEY_NONE;
         const uint64_t in = ballot(key != KEY_NONE && (uint32_t)(key >> 32) == tg);
         n += ~in ? (uint32_t)__builtin_ctzll(~in) : 64u;
@@ -2502,18 +2591,15 @@ __global__ void __launch_bounds__(256) k_group_order(Index ix, GroupArgs g) {
         uint32_t v = l < n ? (uint32_t)g.out[b + l] : NONE;
         wave_sort32(v);
         if (l < n) g.out[b + l] = pair_key(tg, v);
-      } else {  // by rank, through the raw list (free by now)
-        for (uint32_t x = l; x < n; x += 64) {
-          const uint32_t v = (uint32_t)g.out[b + x];
-          uint32_t r = 0;
-          for (uint32_t y = 0; y < n; ++y) r += (uint32_t)g.out[b + y] < v ? 1u : 0u;
-          g.raw[b + r] = pair_key(tg, v);
-        }
-        __threadfence_block();
-        wave_sync();
-        for (uint32_t x = l; x < n; x += 64) g.out[b + x] = g.raw[b + x];
+      } else if (n <= ORDER_WAVE) {
+        order_run(g.out + b, n, mine_keys);
+      } else if (l == 0) {
+        long_at[atomicAdd(&long_n, 1u)] = b;
       }
     }
+    __syncthreads();
+    for (uint32_t k = 0; k < long_n; ++k) order_long_run(g.out + long_at[k], g.raw + long_at[k], np - long_at[k], keys);
+    __syncthreads();
   }
 }
 
