@@ -5200,7 +5200,10 @@ __global__ void __launch_bounds__(64) k_bruteforce_f32(Index ix, const float* q,
 //                 written;
 //   k_bf_near_f32: one wave per query bounds the k-th smallest distance by the
 //                 k-th smallest group minimum and scores the rows of the groups
-//                 at or below the bound (a dozen or so) again, for their keys.
+//                 at or below the bound (a dozen or so) again, for their keys;
+//                 a group that holds nothing before the k-th key so far is left
+//                 out (where distances tie, all of them are at the bound: 1,000
+//                 zero queries on 100,003 rows 5.96 ms without this, 0.54 with).
 // Both add a row's products in the order of the distance batches (lane c of G:
 // the chunks c, G + c, 2G + c in turn, then the lanes in pairs), so distances,
 // bounds and results keep its bits, but for a NaN's sign, which decides whether
@@ -5311,7 +5314,10 @@ __global__ void __launch_bounds__(64) k_bf_near_f32(Index ix, const float* q, ui
   for (uint32_t g0 = 0; g0 < n_grp; g0 += 64) {
     const uint32_t mine = g0 + (uint32_t)l < n_grp ? gm[g0 + (uint32_t)l] : D_INVALID;
     for (uint64_t m = ballot(g0 + (uint32_t)l < n_grp && mine <= bound); m; m &= m - 1ull) {
-      const uint64_t u = (uint64_t)(g0 + (uint32_t)__builtin_ctzll(m)) * 64u + (uint64_t)l;
+      const int e = (int)__builtin_ctzll(m);
+      const uint32_t first = (g0 + (uint32_t)e) * 64u, least = (uint32_t)__builtin_amdgcn_readlane((int)mine, e);
+      if (least > BF_ANY && make_key(least, first) > bcast_lane64(best[0], (int)k - 1)) continue;
+      const uint64_t u = (uint64_t)first + (uint64_t)l;
       bool ok = false;
       if (u < n_ids) {
         const uint64_t r = load_ref(ix, (uint32_t)u);
