@@ -49,3 +49,33 @@ def test_tied_distances_cost_what_others_do():
     want = np.setdiff1d(np.arange(40), gone)[:16]
     assert np.array_equal(i.cpu().numpy(), np.tile(want, (500, 1))) and bool((d == 1.0).all())
     g.close()
+
+
+def _same(a, b):
+    import torch
+    return torch.equal(a[0], b[0]) and torch.equal(a[1].view(torch.int32), b[1].view(torch.int32))
+
+
+# a wave takes 32 queries (16 from 384 dimensions on): batches that end before, at and past a block
+@pytest.mark.parametrize("dim", [96, 192, 384, 768])
+def test_a_batch_gives_what_its_queries_give_alone(dim):
+    import torch
+    g, _, gen = _index(700, dim, dim, max_batch=350)
+    q = torch.randn((33, dim), device="cuda", generator=gen)
+    alone = [g.bruteforce(q[i:i + 1], 16) for i in range(33)]
+    for n in (15, 16, 17, 31, 32, 33):
+        i, d = g.bruteforce(q[:n], 16)
+        assert _same((i, d), (torch.cat([a[0] for a in alone[:n]]), torch.cat([a[1] for a in alone[:n]]))), n
+    g.close()
+
+
+# the group minima of 65,536 rows fill their 256 MiB at 65,536 queries; one group's launch ends at 2^23 queries
+@pytest.mark.parametrize("n,split", [(65_536, 65_536), (64, 1 << 23)])
+def test_more_queries_than_one_launch_holds(n, split):
+    import torch
+    g, _, gen = _index(n, 96, n, max_batch=min(n, 16_384))
+    q = torch.randn((split + 33, 96), device="cuda", generator=gen)
+    i, d = g.bruteforce(q, 5)
+    for b, e in ((0, 40), (split - 40, split), (split - 1, split + 1), (split, split + 33)):
+        assert _same((i[b:e].contiguous(), d[b:e].contiguous()), g.bruteforce(q[b:e].contiguous(), 5)), (b, e)
+    g.close()
