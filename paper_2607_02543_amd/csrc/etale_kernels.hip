@@ -4077,9 +4077,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 // matrix cores give all pairs' products (v_mfma_i32_16x16x64_i8 over the rows
 // shifted to signed bytes, exact as everywhere), each lane tests the pairs it
 // holds of a tile where they are, and the lists are merged by one sort of 64
-// keys in registers. A target with more passing pairs than they take is left,
-// untouched, to the general kernel, through a list of run indices; its reserved
-// slabs stay its own. Bound: vector issue (about 650 instructions per deleted
+// keys in registers. A reverse-edge target with a passing pair or more than
+// fifteen offers, and any without a slab reserved, is left, untouched, to the
+// general kernel, through a list of run indices; its reserved slabs stay its own.
+// Bound: vector issue (about 650 instructions per deleted
 // neighbor, two thirds of the SIMD cycles) and the reads that lead to the rows;
 // 4 waves per SIMD (5 spill: 2.87 -> 3.02 ms per pass). 10,000 deletes and
 // 10,000 inserts at 1M rows, with the general kernels' remainder: repair 2.05 ->
@@ -4097,6 +4098,7 @@ struct CoverLds {
 // shifted norm by 2^27, so a pair with one or two such slots never passes
 constexpr uint32_t COVER_OUT = 1u << 30;
 constexpr uint32_t COVER_BATCH = 4;
+constexpr uint32_t COVER_FEW = 16;  // passing pairs up to which they are gone through one by one
 constexpr uint32_t COVER_LDS = (3 * 64 + COVER_BATCH * 96) * 4;
 
 __device__ inline CoverLds carve_cover(char* smem) {
@@ -4293,30 +4295,53 @@ struct CoverTiles {
     return any != 0;
   }
 
-  // the pairs of a hit word, one by one (rows and columns uniform)
-  template <class Pair>
-  __device__ static void each(uint64_t hit, Pair pair) {
+  // The passing pairs of the hit words by slot: lane l gets the slots whose pair
+  // with slot l passes. A few pairs are gone through one by one (rows and columns
+  // uniform); more of them lane by lane into masks in LDS (where an and thr were),
+  // so that a target with hundreds, as alpha = 1 or rows of few degrees of freedom
+  // give, costs what its fullest lane does. 1,000 deletes of 20,000 x 64-d uniform
+  // rows at alpha = 1: 850 us one by one, 290 now, 355 by the general kernel alone.
+  __device__ static uint64_t passing(const CoverLds& c, uint64_t hit) {
     // tile pair k's g and h, a nibble each
     constexpr uint64_t G_OF = T == 4 ? 0x3221110000ull : 0x211000ull, H_OF = T == 4 ? 0x3323213210ull : 0x221210ull;
-    for (uint64_t lanes = ballot(hit != 0); lanes; lanes &= lanes - 1ull) {
-      const uint32_t e = (uint32_t)__builtin_ctzll(lanes);
-      for (uint64_t w = bcast_lane64(hit, (int)e); w; w &= w - 1ull) {
-        const uint32_t b = (uint32_t)__builtin_ctzll(w), sh = b & ~3u;
-        pair(((uint32_t)(G_OF >> sh) & 15u) * 16u + (e >> 4) * 4u + (b & 3u), ((uint32_t)(H_OF >> sh) & 15u) * 16u + (e & 15u));
+    const uint32_t l = (uint32_t)lane_id();
+    auto row = [&](uint32_t b, uint32_t e) { return ((uint32_t)(G_OF >> (b & ~3u)) & 15u) * 16u + (e >> 4) * 4u + (b & 3u); };
+    auto col = [&](uint32_t b, uint32_t e) { return ((uint32_t)(H_OF >> (b & ~3u)) & 15u) * 16u + (e & 15u); };
+    uint64_t cov = 0;
+    if (bcast(group_sum<64>((uint32_t)__popcll(hit))) <= COVER_FEW) {
+      for (uint64_t lanes = ballot(hit != 0); lanes; lanes &= lanes - 1ull) {
+        const uint32_t e = (uint32_t)__builtin_ctzll(lanes);
+        for (uint64_t w = bcast_lane64(hit, (int)e); w; w &= w - 1ull) {
+          const uint32_t b = (uint32_t)__builtin_ctzll(w), x = row(b, e), y = col(b, e);
+          if (l == x) cov |= 1ull << y;
+          if (l == y) cov |= 1ull << x;
+        }
       }
+      return cov;
     }
+    unsigned long long* const m = reinterpret_cast<unsigned long long*>(c.an);
+    m[l] = 0;
+    wave_sync();
+    for (uint64_t w = hit; w; w &= w - 1ull) {
+      const uint32_t b = (uint32_t)__builtin_ctzll(w), x = row(b, l), y = col(b, l);
+      atomicOr(&m[x], 1ull << y);
+      atomicOr(&m[y], 1ull << x);
+    }
+    wave_sync();
+    cov = m[l];
+    wave_sync();
+    return cov;
   }
 };
 
 // Repair of one target (Algorithm 3): for each deleted u, K = RobustPrune(a,
 // N(u) \ {a}), then the list becomes RobustPrune(a, (N(a) \ {u}) U K), both
 // from the passing pairs alone. Slots 0..31 hold the list, 32..63 N(u); a member
-// of N(u) that is listed takes part in K's prune through its list slot. Returns
-// false, with nothing changed, at a pair (a, u) with more than COVER_MAX.
-constexpr uint32_t COVER_MAX = 512, COVER_DROPS = 8;
+// of N(u) that is listed takes part in K's prune through its list slot.
+constexpr uint32_t COVER_DROPS = 8;
 
 template <int G>
-__device__ inline bool repair_cover_u8(const Index& ix, const MaintArgs& a, const CoverLds& c, uint32_t t,
+__device__ inline void repair_cover_u8(const Index& ix, const MaintArgs& a, const CoverLds& c, uint32_t t,
                                        const RepairHead& hd, int k, uint32_t& n, uint32_t& lid, uint32_t& ld) {
   const uint32_t l = (uint32_t)lane_id();
   const uint32_t R = ix.R;
@@ -4381,21 +4406,18 @@ __device__ inline bool repair_cover_u8(const Index& ix, const MaintArgs& a, cons
     // COVER_DROPS, so only those pairs matter; more drops than that, and all do
     for (uint32_t within = R + COVER_DROPS;; within = 64u) {
       // lane l: the slots whose pair with slot l passes
-      uint64_t cov = 0, hit;
+      uint64_t hit;
       if (!tiles.covers(ix, c, in && (part & 63u) < within, d, hit)) break;
-      if (bcast(group_sum<64>((uint32_t)__popcll(hit))) > COVER_MAX) return false;
-      CoverTiles<G, 4>::each(hit, [&](uint32_t row, uint32_t col) {
-        if (l == row) cov |= 1ull << col;
-        if (l == col) cov |= 1ull << row;
-      });
+      const uint64_t cov = CoverTiles<G, 4>::passing(c, hit);
       // the members of `set` (by slot) that an earlier kept one covers, over the
-      // members of rank mask `rm` in order
+      // members of rank mask `rm` in order (a step per kept one: its ballot drops
+      // the others)
       auto dropped = [&](uint64_t set, uint64_t rm) {
         uint64_t out = 0;
-        for (; rm; rm &= rm - 1ull) {
-          const int s = __builtin_amdgcn_readlane((int)slot, (int)__builtin_ctzll(rm));
-          if ((out >> s) & 1ull) continue;
-          out |= bcast_lane64(cov, s) & set;
+        while (rm) {
+          const uint64_t by = bcast_lane64(cov, __builtin_amdgcn_readlane((int)slot, (int)__builtin_ctzll(rm))) & set;
+          out |= by;
+          rm = (rm & (rm - 1ull)) & ~ballot((by >> slot) & 1ull);
         }
         return out;
       };
@@ -4426,7 +4448,6 @@ __device__ inline bool repair_cover_u8(const Index& ix, const MaintArgs& a, cons
       ld = (uint32_t)__builtin_amdgcn_ds_permute((int)to, (int)ld);
     }
   }
-  return true;
 }
 
 template <int G>
@@ -4473,9 +4494,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
           const uint64_t ra = bcast_lane64(hd.ra, (int)k);
           const uint32_t slab = (uint32_t)__builtin_amdgcn_readlane((int)fresh, (int)k);
           uint32_t n, lid, ld;
-          const bool done = slab != NONE && ref_slab(ra) != NONE &&
-                            repair_cover_u8<G>(ix, a, c, (uint32_t)__builtin_amdgcn_readlane((int)ts, (int)k), hd, (int)k, n,
-                                               lid, ld);
+          const bool done = slab != NONE && ref_slab(ra) != NONE;
+          if (done)
+            repair_cover_u8<G>(ix, a, c, (uint32_t)__builtin_amdgcn_readlane((int)ts, (int)k), hd, (int)k, n, lid, ld);
           if (pend.finish(ix, slabs, tally.pubs)) left.add(ix, a, c, pend.si);
           if (done)
             pend.begin(ix, (uint32_t)(bcast_lane64(hd.pair, (int)k) >> 32), lid, ld, n, ra, b0 + k, slab);

@@ -1,0 +1,90 @@
+"""Repairs and reverse edges where most candidate pairs are covered: rows of few degrees of freedom, repeated rows, and
+alpha = 1. Against the oracle, bit for bit; and their cost beside that of prunes with few covered pairs."""
+
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+from common import assert_same_state
+
+pytestmark = pytest.mark.gpu
+
+
+def rows(rng, n, dim, kind):
+    if kind == "uniform":
+        return rng.integers(0, 256, (n, dim)).astype(np.uint8)
+    if kind == "repeated":
+        return np.random.default_rng(3).integers(0, 256, (60, dim))[rng.integers(0, 60, n)].astype(np.uint8)
+    w = np.random.default_rng(4).standard_normal((2 if kind == "plane" else 4, dim)) * 30
+    return np.clip(np.rint(128 + rng.standard_normal((n, w.shape[0])) @ w), 0, 255).astype(np.uint8)
+
+
+# a few passing pairs, up to sixteen, and hundreds of them; lists that fill the tiles and that do not
+@pytest.mark.parametrize("dim,R,cap,alpha,kind", [
+    (128, 32, None, (1, 1), "uniform"), (128, 32, None, (6, 5), "plane"), (128, 20, 22, (3, 2), "few"),
+    (64, 32, 33, (1, 1), "plane"), (64, 32, None, (2, 1), "few"), (64, 9, None, (1, 1), "repeated"),
+    (32, 32, None, (3, 2), "plane"), (16, 32, 40, (1, 1), "few"), (16, 24, None, (2, 1), "repeated")])
+def test_many_covered_pairs(dim, R, cap, alpha, kind):
+    import torch
+    from paper_2607_02543_amd import etale
+    rng = np.random.default_rng(100 * R + dim)
+    kw = dict(alpha=alpha, n_entry=40, prune_cap=cap)
+    slabs = 9000 + 600 * (R + 2)
+    o = oracle.Oracle(oracle.METRIC_L2_U8, dim, R, 40, 3000, slabs, **kw)
+    g = etale.Index(dim, R=R, L_build=40, id_capacity=3000, slab_capacity=slabs, max_batch=600, **kw)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    live, nxt = np.zeros(0, np.int64), 0
+
+    def insert(n):
+        nonlocal live, nxt
+        x = rows(rng, n, dim, kind)
+        o.insert(x)
+        g.insert(up(x))
+        live = np.concatenate([live, np.arange(nxt, nxt + n)])
+        nxt += n
+        assert_same_state(o, g, f"{nxt} inserted")
+
+    for n in (90, 300, 600):
+        insert(n)
+    for r in range(4):
+        dl = rng.permutation(live)[:len(live) // 5].astype(np.uint32)
+        live = np.setdiff1d(live, dl)
+        o.delete(dl)
+        g.delete(up(dl.astype(np.int32)))
+        assert_same_state(o, g, f"delete {r}")
+        insert(200)
+        if r % 2:
+            o.reclaim()
+            g.reclaim()
+            assert_same_state(o, g, f"reclaim {r}")
+    g.close()
+
+
+def test_many_covered_pairs_cost_what_few_do():
+    import torch
+    from paper_2607_02543_amd import etale
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    x = torch.randint(0, 256, (20_000, 64), dtype=torch.uint8, device="cuda", generator=gen)
+
+    def us(alpha):
+        g = etale.Index(64, R=32, L_build=64, n_entry=1024, id_capacity=20_000, slab_capacity=200_000, max_batch=2000,
+                        alpha=alpha, W=2)
+        for b in range(0, 20_000, 2000):
+            g.insert(x[b:b + 2000])
+        best = 1e9
+        for b in range(0, 6000, 1000):
+            ids = torch.arange(b, b + 1000, dtype=torch.int32, device="cuda")
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            g.delete(ids)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        g.close()
+        return best * 1e6
+
+    few, many = us((2, 1)), us((1, 1))
+    print(f"[repair] few covered pairs {few:.0f} us, many {many:.0f} us", flush=True)
+    assert many < 1.6 * few  # going through them one by one takes two and a half times as long
