@@ -96,8 +96,8 @@ typedef struct {
   uint32_t tombstone_only;   /* 1: delete only flags; no repair, no reclaim */
   uint32_t publish_attempts; /* CAS attempt budget of one publication */
   uint32_t max_batch;        /* largest insert / delete batch of one call */
-  uint32_t vt_slots;         /* visited-table slots per search (power of two); a launch may
-                                take more, up to 4096, where the chip has room for them */
+  uint32_t vt_slots;         /* visited-table slots per search (power of two, 64..16384); 1024, the
+                                default, lets each launch take up to 4096 where that is faster */
   uint32_t waves_per_block;  /* search wavefronts per workgroup */
   int32_t metric;            /* ETALE_METRIC_* */
   int32_t traversal;         /* ETALE_TRAV_* (float metric only) */
@@ -360,8 +360,10 @@ etale_status etale_serve(etale_t ix, const etale_serve_config* cfg, const etale_
 
 /* Result-invariant launch knobs of the beam search: waves per workgroup (1,
  * 2 or 4; halved further while a workgroup's LDS would exceed 64 KiB) and
- * visited-table slots (a power of two, 64..16384; the table may forget ids,
- * which only repeats distance evaluations). Rounds captured as graphs are
+ * visited-table slots (a power of two, 64..16384, as in the config: 1024 is the
+ * library's choice per launch, from 1024 to 4096 by the launch's size and L, any
+ * other count is taken as it is; the table may forget ids, which only repeats
+ * distance evaluations). Rounds captured as graphs are
  * keyed by these values, so a change never alters a captured round. */
 etale_status etale_set_search_knobs(etale_t ix, uint32_t waves_per_block, uint32_t vt_slots);
 
@@ -373,7 +375,7 @@ etale_status etale_set_search_lanes(etale_t ix, uint32_t lanes_per_row);
 
 typedef struct {
   uint32_t waves_per_block;
-  uint32_t vt_slots;
+  uint32_t vt_slots;   /* as for etale_set_search_knobs (1024: chosen per launch) */
   uint32_t row_lanes;  /* lanes per uint8 row (0 for float rows) */
   float ms;            /* mean search time of the chosen setting on the batch */
   float ms_default;    /* the same for the setting in force before the call */
@@ -381,8 +383,10 @@ typedef struct {
 
 /* Autotuner: times the query search on the caller's batch (q_dev [nq x dim],
  * k, L) for every setting of the result-invariant knobs above (waves 1/2/4 x
- * visited slots 256..4096 x lanes per row) and keeps the fastest; results do
- * not depend on the choice. Allocates its own output scratch; synchronizes. */
+ * visited slots 256..4096 x lanes per row; a count that the default comes to
+ * for this batch is not timed twice) and keeps the fastest, the setting in force
+ * where none is faster; results do not depend on the choice. Allocates its own
+ * output scratch; synchronizes. */
 etale_status etale_autotune(etale_t ix, const void* q_dev, uint64_t nq, uint32_t k, uint32_t L,
                             etale_tune_result* out_host);
 

@@ -216,9 +216,9 @@ uint32_t search_waves_per_block(const etale_index* ix, uint32_t lds_per_wave) {
   return w;
 }
 
-// Visited-table slots of a search launch over nq queries: at least the
-// configured count, and up to 4,096 (results do not depend on it) where more
-// cost nothing or pay for themselves.
+// Visited-table slots of a search launch over nq queries: the configured count,
+// but where that is the default, 1,024, up to 4,096 (results do not depend on
+// it) where more cost nothing or pay for themselves.
 // - Float rows: the largest power of two up to (L + 2) R, the ids a search
 //   offers when its neighborhoods hardly overlap (embeddings spread over the
 //   sphere). A table that fills up makes every further id a repeated distance
@@ -231,10 +231,11 @@ uint32_t search_waves_per_block(const etale_index* ix, uint32_t lds_per_wave) {
 //   (a step's 64 ids: 3,700 -> 1,430 cycles at 96-d float, 1,700 -> 900 at
 //   uint8). Where the waves are bound by LDS the configured count stays:
 //   10,000 uint8 queries take 383 us at 1,024 slots and 450 at 2,048.
-constexpr uint32_t VT_MAX = 4096;
+constexpr uint32_t VT_DEFAULT = 1024, VT_MAX = 4096;
 constexpr uint64_t CHIP_LDS = 256ull * 160 * 1024;
 uint32_t search_vt_slots(const etale_index* ix, uint32_t L, uint64_t nq) {
   uint32_t v = ix->cfg.vt_slots;
+  if (v != VT_DEFAULT) return v;
   const uint64_t ids = (uint64_t)(L + 2) * ix->cfg.R;
   if (ix->cfg.metric == ETALE_METRIC_IP_F32)
     while (v < VT_MAX && 2 * v <= ids) v *= 2;
@@ -1647,10 +1648,16 @@ etale_status etale_autotune(etale_t ix, const void* q_dev, uint64_t nq, uint32_t
   const uint32_t slots[] = {256, 512, 1024, 2048, 4096};
   std::vector<uint32_t> lanes = {0};
   if (ix->cfg.metric == ETALE_METRIC_L2_U8 && (ix->cfg.dim == 128 || ix->cfg.dim == 256)) lanes.push_back(ix->cfg.dim / 32);
+  // what the default's slots come to for this batch: the same launch, timed once
+  ix->cfg.vt_slots = VT_DEFAULT;
+  const uint32_t same = search_vt_slots(ix, L, std::min<uint64_t>(nq, library_scratch(ix, ix->cfg.n_entry).chunk));
+  ix->cfg.vt_slots = vt0;
   for (uint32_t rl : lanes)
     for (uint32_t w : waves)
       for (uint32_t v : slots) {
         if (st) break;
+        if (v != VT_DEFAULT && v == same) continue;
+        if (w == wpb0 && v == vt0 && rl == rl0) continue;  // in force: timed above, and kept on a tie
         if (search_lds_per_wave(L, v, ix->cfg.W) > 65536u) continue;
         float ms = 0.f;
         st = time_one(w, v, rl, &ms);
