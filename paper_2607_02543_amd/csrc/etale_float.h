@@ -93,14 +93,16 @@ __device__ inline float group_sum8(const float (&v)[8]) {
 }
 
 // ---- traversal distance: G lanes per row, 3 chunks per lane --------------------------------
-template <int G, int TRAV>
+// UMAX: rows per lane group in flight at most (the re-rank, once per query, takes
+// four, so that it does not set its kernel's registers)
+template <int G, int TRAV, int UMAX = 8>
 struct TravF {
   static constexpr int EPC = TRAV == TRAV_NATIVE ? 4 : (TRAV == TRAV_BF16 ? 8 : 16);  // elements per chunk
   static constexpr int CPL = 3;
   static constexpr int VPP = 64 / G;
   // rows per lane group in flight together: eight where eight lanes or more
   // share a row (their sums are then reduced together), 64 rows in all below
-  static constexpr int U = G >= 8 ? 8 : G;
+  static constexpr int U = G < UMAX ? G : UMAX;
   struct Q {
     float v[CPL][EPC];
   };
@@ -166,6 +168,30 @@ struct TravF {
     return TRAV == TRAV_FP8 ? ix.xs[id] * 256.0f : 1.0f;
   }
 
+  // The keys of rows [from, to) of a batch with a NaN in it: from a NaN code, which
+  // FP8 decodes by bit pattern, or from the vectors, and then its sign (by which it
+  // sorts first or last) hangs on the order of the sum. Both are settled a row at
+  // a time, as lane 0 of the row's group sums it. (The lane's number is read
+  // again: kept for this it takes a register of the sum's, and some searches a
+  // wave per SIMD.)
+  __device__ static void settle_nans(const Index& ix, const Q& q, const uint32_t* ids, int from, int to, uint64_t* ck) {
+    int ln;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+    const int cl = ln % G;
+#pragma unroll 1
+    for (int base = from; base < to; base += VPP) {
+      const int vi = base + ln / G;
+      uint4 x[CPL];
+#pragma unroll
+      for (int t = 0; t < CPL; ++t) x[t] = vi < to ? row(ix, ids[vi])[t * G + cl] : make_uint4(0, 0, 0, 0);
+      const float d = group_sum_t<G, float>(partial<TRAV == TRAV_FP8>(q, x));
+      if (cl == 0 && vi < to) ck[vi] = make_key(fkey(1.0f - scale(ix, ids[vi]) * d), ids[vi]);
+    }
+  }
+  // looked for after every pass where a pass takes most of a batch, else at its end
+  // (768-d FP32, 100 queries, L = 64: 575 us after every pass, 550; 96-d 161 and 165)
+  static constexpr bool PER_PASS = G <= 16;
+
   // Keys (d, id) of ids[0..cnt) and, if cr, their reference words. The batch is
   // bound by the latency of its gathers, so U VPP rows are in flight together
   // (2 VPP before), and for FP8 was bound by decoding each code in six
@@ -178,6 +204,7 @@ struct TravF {
                                     uint64_t* cr) {
     const int l = lane_id();
     const int c = l % G, grp = l / G;
+    bool nan = false;
     for (int base = 0; base < cnt; base += U * VPP) {
       const int used = min(U, (cnt - base + VPP - 1) / VPP);  // the others are skipped (uniform branches)
       uint4 w[U][CPL];
@@ -218,30 +245,18 @@ struct TravF {
           if (c == u) dot = d;
         }
       }
-      const uint64_t nan = ballot(mine && dot != dot);
+      nan = nan || (mine && dot != dot);
       if (mine) {
         ck[my] = make_key(fkey(1.0f - sc * dot), id);
         if (cr) cr[my] = r;
       }
-      // A NaN: from a NaN code, which FP8 decodes by bit pattern, or from the
-      // vectors, and then its sign (by which it sorts first or last) hangs on
-      // the order of the sum. Both are settled a row at a time, as lane 0 of
-      // the row's group sums it. (The lane's number is read again: kept for this
-      // it takes a register of the sum's, and some searches a wave per SIMD.)
-      if (__builtin_expect(nan != 0, 0)) {
-        int ln;
-        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
-        const int cl = ln % G;
-#pragma unroll 1
-        for (int u = 0; u < used; ++u) {
-          const int vi = base + u * VPP + ln / G;
-          uint4 x[CPL];
-#pragma unroll
-          for (int t = 0; t < CPL; ++t) x[t] = vi < cnt ? row(ix, ids[vi])[t * G + cl] : make_uint4(0, 0, 0, 0);
-          const float d = group_sum_t<G, float>(partial<TRAV == TRAV_FP8>(q, x));
-          if (cl == 0 && vi < cnt) ck[vi] = make_key(fkey(1.0f - scale(ix, ids[vi]) * d), ids[vi]);
-        }
+      if constexpr (PER_PASS) {
+        if (__builtin_expect(ballot(nan) != 0, 0)) settle_nans(ix, q, ids, base, min(cnt, base + U * VPP), ck);
+        nan = false;
       }
+    }
+    if constexpr (!PER_PASS) {
+      if (__builtin_expect(ballot(nan) != 0, 0)) settle_nans(ix, q, ids, 0, cnt, ck);
     }
   }
 };

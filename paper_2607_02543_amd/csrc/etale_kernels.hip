@@ -1239,6 +1239,7 @@ uint32_t scan_select_lds_per_wave(uint32_t L) { return 8u * scan_select_keys(L);
 template <int G, int C = 1>
 struct TravU8 {
   static constexpr bool FLOAT = false;
+  static constexpr unsigned WPE = 1, WPE_LDS = 1;
   struct Q {
     uint4 f[C];
     uint32_t qq;
@@ -1283,8 +1284,12 @@ struct TravFloat {
   static constexpr int MODE = TRAV;
   using T = TravF<G, TRAV>;
   using Q = typename T::Q;
+  // waves per SIMD: three where the kernels fit 168 registers, or nearly (a few
+  // spill, outside the distance batches); FP8 rows over more lanes take over 190
+  static constexpr unsigned WPE = TRAV == TRAV_FP8 && G > 4 ? 2 : 3;
+  static constexpr unsigned WPE_LDS = TRAV != TRAV_NATIVE && G > 4 ? 2 : 3;  // lists in LDS: bf16 spills twice as many
   static constexpr int GF = G * T::EPC / 4;  // lanes per row of the FP32 copy
-  using Exact = TravF<GF, TRAV_NATIVE>;
+  using Exact = TravF<GF, TRAV_NATIVE, 4>;
   __device__ static Q load_query(const void* row) { return T::load_query(reinterpret_cast<const float*>(row)); }
   __device__ static const void* stored_row(const Index& ix, uint32_t id) { return ix.xf + (size_t)id * ix.dim; }
   __device__ static size_t query_bytes(const Index& ix) { return (size_t)ix.dim * 4; }
@@ -1895,7 +1900,7 @@ __device__ inline void search_kernel(const Index& ix, SearchArgs& a, char* smem)
 
 // list in registers; uint8 rows hold their registers to 7 waves per SIMD (the
 // LDS of 7 four-wave blocks fits a CU at the default visited-table size),
-// float rows keep theirs (they would spill). Q: query searches (results out)
+// float rows to TravFloat::WPE. Q: query searches (results out)
 // or insert searches (expanded sets out), compiled apart so that each keeps
 // only its own output code and each has a kernel name of its own.
 template <class TP, unsigned WPE, int H, bool Q>
@@ -1915,7 +1920,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
 }
 
 template <class TP, bool Q>
-__global__ void __launch_bounds__(256) k_search(Index ix, SearchArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TP::WPE_LDS))) k_search(Index ix, SearchArgs a) {
   extern __shared__ __align__(16) char smem[];
   a.mode = Q ? MODE_QUERY : MODE_INSERT;
   search_kernel<TP, false, 1>(ix, a, smem);
@@ -5622,13 +5627,13 @@ hipError_t launch_scan(const Index& ix, const ScanArgs& args, hipStream_t s, hip
   do {                                                                                                          \
     if (a.L <= 64)                                                                                              \
       if (a.W > 2)                                                                                              \
-        hipLaunchKernelGGL((k_search_rl<TP, TP::FLOAT ? 1u : 6u, 2, Q>), dim3(grid), dim3(64 * waves_per_block), lds, \
+        hipLaunchKernelGGL((k_search_rl<TP, TP::FLOAT ? TP::WPE : 6u, 2, Q>), dim3(grid), dim3(64 * waves_per_block), lds, \
                            s, ix, a);                                                                           \
       else                                                                                                      \
-        hipLaunchKernelGGL((k_search_rl<TP, TP::FLOAT ? 1u : 7u, 1, Q>), dim3(grid), dim3(64 * waves_per_block), lds, \
+        hipLaunchKernelGGL((k_search_rl<TP, TP::FLOAT ? TP::WPE : 7u, 1, Q>), dim3(grid), dim3(64 * waves_per_block), lds, \
                            s, ix, a);                                                                           \
     else if (a.L <= 128 && a.W <= 2)                                                                            \
-      hipLaunchKernelGGL((k_search_rl2<TP, TP::FLOAT ? 1u : 6u, Q>), dim3(grid), dim3(64 * waves_per_block), lds, \
+      hipLaunchKernelGGL((k_search_rl2<TP, TP::FLOAT ? TP::WPE : 6u, Q>), dim3(grid), dim3(64 * waves_per_block), lds, \
                          s, ix, a);                                                                             \
     else                                                                                                        \
       hipLaunchKernelGGL((k_search<TP, Q>), dim3(grid), dim3(64 * waves_per_block), lds, s, ix, a);             \
