@@ -222,24 +222,33 @@ uint32_t search_waves_per_block(const etale_index* ix, uint32_t lds_per_wave) {
 // - Float rows: the largest power of two up to (L + 2) R, the ids a search
 //   offers when its neighborhoods hardly overlap (embeddings spread over the
 //   sphere). A table that fills up makes every further id a repeated distance
-//   and a check for repeats; registers, not LDS, bound the resident waves.
-//   3,001 queries, 96-d, L = 64, R = 32: 562 us at 1,024 slots, 483 at 2,048,
-//   496 at 4,096, 595 at 8,192; 2,000 queries, 768-d FP8, L = 96, R = 48:
-//   1,600 / 1,390 / 1,070 / 1,590.
+//   and a check for repeats. Lists in registers: registers, not LDS, bound the
+//   resident waves. 3,001 queries, 96-d, L = 64, R = 32: 562 us at 1,024 slots,
+//   483 at 2,048, 496 at 4,096, 595 at 8,192; 2,000 queries, 768-d FP8, L = 96,
+//   R = 48: 1,600 / 1,390 / 1,070 / 1,590. Lists in LDS: there it is LDS, and more
+//   slots pay only where a repeated distance is dear, in FP8 rows and rows of 3
+//   KB, and while six waves still fit a CU. 3,000 queries, R = 32, at 1,024 / 2,048
+//   / 4,096 slots: 768-d FP32, L = 160, 4,010 / 3,730 / 3,040; 384-d FP8 2,440 /
+//   2,100 / 1,720, and L = 256 3,880 / 3,720 / 4,360; but 384-d FP32 2,060 / 2,570
+//   / 2,090, 96-d FP32, R = 16, 1,130 / 1,550 / 1,420.
 // - Launches whose waves all fit the chip's LDS with twice the slots, up to
 //   twice those ids: a sparse table settles almost every id on its first try
 //   (a step's 64 ids: 3,700 -> 1,430 cycles at 96-d float, 1,700 -> 900 at
 //   uint8). Where the waves are bound by LDS the configured count stays:
 //   10,000 uint8 queries take 383 us at 1,024 slots and 450 at 2,048.
 constexpr uint32_t VT_DEFAULT = 1024, VT_MAX = 4096;
-constexpr uint64_t CHIP_LDS = 256ull * 160 * 1024;
-uint32_t search_vt_slots(const etale_index* ix, uint32_t L, uint64_t nq) {
+constexpr uint64_t CU_LDS = 160 * 1024, CHIP_LDS = 256 * CU_LDS;
+uint32_t search_vt_slots(const etale_index* ix, uint32_t L, uint64_t nq, int32_t trav) {
   uint32_t v = ix->cfg.vt_slots;
   if (v != VT_DEFAULT) return v;
+  const uint32_t W = ix->cfg.W;
   const uint64_t ids = (uint64_t)(L + 2) * ix->cfg.R;
-  if (ix->cfg.metric == ETALE_METRIC_IP_F32)
-    while (v < VT_MAX && 2 * v <= ids) v *= 2;
-  while (v < VT_MAX && v <= ids && nq * search_lds_per_wave(L, 2 * v, ix->cfg.W) <= CHIP_LDS) v *= 2;
+  if (ix->cfg.metric == ETALE_METRIC_IP_F32) {
+    const bool regs = L <= 64 || (L <= 128 && W <= 2);
+    const bool dear = trav != ETALE_TRAV_NATIVE || ix->cfg.dim * 4 >= 3072;
+    while (v < VT_MAX && 2 * v <= ids && (regs || (dear && 6 * search_lds_per_wave(L, 2 * v, W) <= CU_LDS))) v *= 2;
+  }
+  while (v < VT_MAX && v <= ids && nq * search_lds_per_wave(L, 2 * v, W) <= CHIP_LDS) v *= 2;
   return v;
 }
 
@@ -388,7 +397,7 @@ etale_status run_searches(etale_index* ix, int mode, const uint8_t* q, uint64_t 
     sa.L = L;
     sa.k = k;
     sa.vcap = vcap;
-    const uint32_t vt = search_vt_slots(ix, L, cn);
+    const uint32_t vt = search_vt_slots(ix, L, cn, sc.trav);
     sa.vt_mask = vt - 1;
     sa.W = ix->cfg.W;
     sa.lds_per_wave = search_lds_per_wave(L, vt, ix->cfg.W);
@@ -1650,7 +1659,8 @@ etale_status etale_autotune(etale_t ix, const void* q_dev, uint64_t nq, uint32_t
   if (ix->cfg.metric == ETALE_METRIC_L2_U8 && (ix->cfg.dim == 128 || ix->cfg.dim == 256)) lanes.push_back(ix->cfg.dim / 32);
   // what the default's slots come to for this batch: the same launch, timed once
   ix->cfg.vt_slots = VT_DEFAULT;
-  const uint32_t same = search_vt_slots(ix, L, std::min<uint64_t>(nq, library_scratch(ix, ix->cfg.n_entry).chunk));
+  const uint32_t same = search_vt_slots(ix, L, std::min<uint64_t>(nq, library_scratch(ix, ix->cfg.n_entry).chunk),
+                                        ix->qtrav);
   ix->cfg.vt_slots = vt0;
   for (uint32_t rl : lanes)
     for (uint32_t w : waves)

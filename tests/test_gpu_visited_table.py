@@ -50,3 +50,32 @@ def test_a_set_count_is_the_one_that_runs(metric, dim, W, L):
         assert torch.equal(few[1], many[1]) and torch.equal(few[2], many[2])
         assert few[0] > 1.2 * many[0], (few[0], many[0])
     assert scored[True, 64][0] == scored[False, 64][0] and scored[True, 4096][0] == scored[False, 4096][0]
+
+
+# lists in LDS: where that bounds the resident waves a large table costs more than it saves, unless a distance is dear
+@pytest.mark.parametrize("dim,trav,W,L", [(96, 0, 1, 160), (96, 0, 4, 100), (768, 0, 1, 160), (384, 2, 1, 160)])
+def test_the_default_is_no_slower_than_a_set_count(dim, trav, W, L):
+    import torch
+    n = 30_000 if dim == 96 else 8000
+    g, make = _index(dim, n, 6, R=16 if dim == 96 else 32, L_build=48, n_entry=1024, W=W, metric=1, traversal=trav)
+    q = make(3000)
+
+    def us():
+        best = 1e9
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            g.search(q, 10, L)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        return best * 1e6
+
+    default, found = us(), g.search(q, 10, L)
+    others = {}
+    for slots in (512, 2048, 4096):
+        g.set_search_knobs(4, slots)
+        others[slots] = us()
+        assert all(torch.equal(a, b) for a, b in zip(found, g.search(q, 10, L)))
+    print(f"[visited] {dim}-d {trav} W={W} L={L}: default {default:.0f} us, set {others}", flush=True)
+    assert default < 1.15 * min(others.values())
+    g.close()
