@@ -226,8 +226,9 @@ uint32_t search_waves_per_block(const etale_index* ix, uint32_t lds_per_wave) {
 //   resident waves. 3,001 queries, 96-d, L = 64, R = 32: 562 us at 1,024 slots,
 //   483 at 2,048, 496 at 4,096, 595 at 8,192; 2,000 queries, 768-d FP8, L = 96,
 //   R = 48: 1,600 / 1,390 / 1,070 / 1,590. Lists in LDS: there it is LDS, and more
-//   slots pay only where a repeated distance is dear, in FP8 rows and rows of 3
-//   KB, and while six waves still fit a CU. 3,000 queries, R = 32, at 1,024 / 2,048
+//   slots pay only where a repeated distance is dear or registers hold the waves
+//   to as few, in bf16 and FP8 copies and rows of 3 KB, and while six waves still
+//   fit a CU. 3,000 queries, R = 32, at 1,024 / 2,048
 //   / 4,096 slots: 768-d FP32, L = 160, 4,010 / 3,730 / 3,040; 384-d FP8 2,440 /
 //   2,100 / 1,720, and L = 256 3,880 / 3,720 / 4,360; but 384-d FP32 2,060 / 2,570
 //   / 2,090, 96-d FP32, R = 16, 1,130 / 1,550 / 1,420.

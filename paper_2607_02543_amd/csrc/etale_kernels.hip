@@ -4647,55 +4647,64 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
 // ---- reclaim (Algorithm 4) -------------------------------------------------------------
 // live nodes with an edge into a tombstone ("dirty"), and the count of such
 // edges. Every neighbor of every live node is looked up in the deletion bitmap,
-// 32 random words per node: each workgroup keeps the bitmap in LDS (up to 2^20
-// ids; past that folded onto 2^20 bits, and a set bit is looked up again in
-// memory), where a wave's 64 lookups take a few cycles instead of one L2 line
-// each. 1,000,000 nodes, R = 32, reclaim after 10,000 deletes: 127 us with the
-// lookups in memory, 67 now (136 MB of words and lists, 2 TB/s: what is left is
-// latency, 16 waves per CU); 12,000 nodes, R = 48: 60, now 14.
-constexpr uint32_t DIRTY_WAVES = 16, DIRTY_RUNS = 4;  // waves per workgroup, runs of 64 nodes per wave and step at most
+// 32 random words per node: each workgroup keeps the bitmap in LDS (as many bits
+// as a power of two past the ids, up to 2^20; past that folded onto 2^20, and a
+// set bit is looked up again in memory), where a wave's 64 lookups take a few
+// cycles instead of one L2 line each. Ids are not used again, so the deleted ones
+// add up over an index's life: once they would set more than one folded bit in
+// four, nothing is copied and every lookup goes to memory. No more workgroups
+// than fit the chip at once, so that each copies the bitmap once. Reclaim after
+// 10,000 deletes, R = 32, 1,000,000 nodes, in us by ids handed out (memory alone |
+// before | now): 1.04 M 340 | 200 | 197; 2 M 350 | 275 | 263; 3.5 M 367 | 334 | 270.
+// Bound by latency at 16 waves per CU (136 MB of words and lists at 1 M).
+constexpr uint32_t DIRTY_WAVES = 16, DIRTY_RUNS = 4;  // waves per workgroup, chunks of 64 nodes per wave between publications
 constexpr uint32_t DIRTY_BITS = 1u << 20;
+constexpr uint32_t DIRTY_STEP = 64 * DIRTY_WAVES;  // nodes of a chunk
 
 __global__ void __launch_bounds__(64 * DIRTY_WAVES) k_dirty(Index ix, uint64_t n_ids, Dyn d, uint32_t* dirty,
-                                                            uint32_t runs) {
-  __shared__ uint32_t bits[DIRTY_BITS / 32];
-  __shared__ uint32_t buf[64 * DIRTY_WAVES * DIRTY_RUNS];
+                                                            uint32_t n_bits) {
+  extern __shared__ uint32_t bits[];  // [n_bits / 32]
+  __shared__ uint32_t buf[DIRTY_STEP * DIRTY_RUNS];
   __shared__ uint32_t cnt_s, dead_s, base_s;
   if (gated(ix, d)) return;
   const uint32_t n = dyn_count(ix, d, (uint32_t)n_ids);
   const uint32_t R = ix.R;
-  const uint32_t step = 64u * DIRTY_WAVES * runs;
-  if ((uint64_t)blockIdx.x * step >= n) return;
-  const uint32_t words = (n + 31u) / 32u, fold = min(words, DIRTY_BITS / 32u);  // an id's bit: id % DIRTY_BITS
-  const uint32_t* src = reinterpret_cast<const uint32_t*>(ix.delbits);
-  for (uint32_t i = threadIdx.x; i < fold; i += blockDim.x) {
-    uint32_t v = src[i];
-    for (uint32_t w = i + DIRTY_BITS / 32u; w < words; w += DIRTY_BITS / 32u) v |= src[w];
-    bits[i] = v;
+  if ((uint64_t)blockIdx.x * DIRTY_STEP >= n) return;
+  const bool exact = n <= n_bits;
+  const bool copied = exact || ix.ctr[C_TOMBSTONED] <= n_bits / 4u;
+  if (copied) {  // an id's bit: id % n_bits
+    const uint32_t words = (n + 31u) / 32u, fold = min(words, n_bits / 32u);
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(ix.delbits);
+    for (uint32_t i = threadIdx.x; i < fold; i += blockDim.x) {
+      uint32_t v = src[i];
+      for (uint32_t w = i + n_bits / 32u; w < words; w += n_bits / 32u) v |= src[w];
+      bits[i] = v;
+    }
   }
-  const bool exact = n <= DIRTY_BITS;
   auto deleted = [&](uint32_t id) -> uint32_t {
-    const uint32_t at = id & (DIRTY_BITS - 1u);
-    bool hit = (bits[at >> 5] >> (at & 31u)) & 1u;
+    const uint32_t at = id & (n_bits - 1u);
+    bool hit = !copied || ((bits[at >> 5] >> (at & 31u)) & 1u);
     if (hit && !exact) hit = del_bit(ix, id);
     return hit ? 1u : 0u;
   };
-  // A workgroup takes 1,024 nodes per run and up to four runs per step, lane l
-  // of a wave owning node base + l. The slabs are read by eight lanes per node, eight
+  // A workgroup takes every gridDim-th chunk of 1,024 nodes, four of them between
+  // publications, lane l of a wave owning node base + l. The slabs are read by eight lanes per node, eight
   // nodes at a time (lane c of a group reads ids 4c.. 4c+3, then 32 further
   // on), so a node's id half is one contiguous run; each group's count goes
   // to its node's lane. Dirty ids gather in LDS and take their place in the
-  // list with one atomic per workgroup and step.
+  // list with one atomic per workgroup and four chunks.
   const int l = lane_id();
   const uint32_t c = (uint32_t)(l & 7), wv = threadIdx.x >> 6;
-  for (uint32_t chunk = blockIdx.x; (uint64_t)chunk * step < n; chunk += gridDim.x) {
+  for (uint64_t chunk = blockIdx.x; chunk * DIRTY_STEP < n; chunk += (uint64_t)DIRTY_RUNS * gridDim.x) {
     if (threadIdx.x == 0) {
       cnt_s = 0;
       dead_s = 0;
     }
     __syncthreads();
-    for (uint32_t run = 0; run < runs; ++run) {
-      const uint32_t base = chunk * step + (run * DIRTY_WAVES + wv) * 64u;
+    for (uint32_t run = 0; run < DIRTY_RUNS; ++run) {
+      const uint64_t base64 = (chunk + (uint64_t)run * gridDim.x) * DIRTY_STEP + wv * 64u;
+      if (base64 >= n) break;
+      const uint32_t base = (uint32_t)base64;
       // The run's reference words are read in one coalesced load (lane l: node
       // base + l) and the eight groups' slab reads are all issued before the
       // first lookup, so the dependent reads of a node overlap with those of
@@ -5895,13 +5904,12 @@ hipError_t launch_tombstone(const Index& ix, const uint32_t* dlist, uint32_t n, 
 
 hipError_t launch_dirty(const Index& ix, uint64_t n_ids, Dyn d, uint32_t* dirty, hipStream_t s) {
   if (n_ids == 0) return hipSuccess;
-  // as many runs per step as leave each CU a workgroup: every step ends in two
-  // atomics on the same words
-  const uint32_t per_run = 64 * DIRTY_WAVES;
-  const uint32_t runs = (uint32_t)std::min<uint64_t>(DIRTY_RUNS, std::max<uint64_t>(1, n_ids / (256ull * per_run)));
-  const unsigned blocks = blocks_for(n_ids, per_run * runs);
-  hipLaunchKernelGGL(k_dirty, dim3(blocks < PERSIST_BLOCKS ? blocks : PERSIST_BLOCKS), dim3(per_run), 0, s, ix, n_ids, d,
-                     dirty, runs);
+  uint32_t n_bits = 64 * DIRTY_WAVES;
+  while (n_bits < DIRTY_BITS && n_bits < n_ids) n_bits <<= 1;
+  const dim3 blk(DIRTY_STEP);
+  const unsigned sh = ix.concurrent ? 2u : 1u;
+  hipLaunchKernelGGL(k_dirty, resident_grid(k_dirty, blocks_for(n_ids, DIRTY_STEP), blk, n_bits / 8, sh), blk, n_bits / 8, s,
+                     ix, n_ids, d, dirty, n_bits);
   return hipGetLastError();
 }
 
