@@ -238,7 +238,7 @@ uint32_t search_waves_per_block(const etale_index* ix, uint32_t lds_per_wave) {
 //   uint8). Where the waves are bound by LDS the configured count stays:
 //   10,000 uint8 queries take 383 us at 1,024 slots and 450 at 2,048.
 constexpr uint32_t VT_DEFAULT = 1024, VT_MAX = 4096;
-constexpr uint64_t CU_LDS = 160 * 1024, CHIP_LDS = 256 * CU_LDS;
+constexpr uint64_t CU_LDS = 160 * 1024;
 uint32_t search_vt_slots(const etale_index* ix, uint32_t L, uint64_t nq, int32_t trav) {
   uint32_t v = ix->cfg.vt_slots;
   if (v != VT_DEFAULT) return v;
@@ -249,7 +249,7 @@ uint32_t search_vt_slots(const etale_index* ix, uint32_t L, uint64_t nq, int32_t
     const bool dear = trav != ETALE_TRAV_NATIVE || ix->cfg.dim * 4 >= 3072;
     while (v < VT_MAX && 2 * v <= ids && (regs || (dear && 6 * search_lds_per_wave(L, 2 * v, W) <= CU_LDS))) v *= 2;
   }
-  while (v < VT_MAX && v <= ids && nq * search_lds_per_wave(L, 2 * v, W) <= CHIP_LDS) v *= 2;
+  while (v < VT_MAX && v <= ids && nq * search_lds_per_wave(L, 2 * v, W) <= device_cus() * CU_LDS) v *= 2;
   return v;
 }
 

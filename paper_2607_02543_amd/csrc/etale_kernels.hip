@@ -5380,6 +5380,18 @@ __global__ void __launch_bounds__(64) k_bf_near_f32(Index ix, const float* q, ui
 
 static inline unsigned blocks_for(uint64_t n, unsigned per) { return (unsigned)((n + per - 1) / per); }
 
+// CUs of the current device (256 on a whole MI355X), read once; 256 if it does not say
+unsigned device_cus() {
+  static const unsigned n = [] {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+      return 256u;
+    return (unsigned)cus;
+  }();
+  return n;
+}
+
 // Item loops run on persistent waves: a launch never needs more workgroups
 // than this (the chip holds 256 CUs x a few workgroups; the rest would queue).
 constexpr unsigned PERSIST_BLOCKS = 2048;
@@ -5545,8 +5557,8 @@ static bool launch_scan_tile_f(const Index& ix, const ScanArgs& a, uint64_t leas
 // (146 against 22 us); with 512 or 1,024 tiles asked for the same within 1%.
 template <int TRAV>
 static void launch_scan_dist_f(const Index& ix, const ScanArgs& a, hipStream_t s) {
-  constexpr uint64_t CUS = 256;
-  if (launch_scan_tile_f<TRAV, 8, 8, 4>(ix, a, CUS, s) || launch_scan_tile_f<TRAV, 4, 4, 8>(ix, a, CUS, s)) return;
+  const uint64_t cus = device_cus();
+  if (launch_scan_tile_f<TRAV, 8, 8, 4>(ix, a, cus, s) || launch_scan_tile_f<TRAV, 4, 4, 8>(ix, a, cus, s)) return;
   (void)launch_scan_tile_f<TRAV, 2, 2, 8>(ix, a, 0, s);
 }
 
@@ -5733,15 +5745,12 @@ static unsigned resident_blocks(F f, unsigned threads, size_t lds) {
   };
   static std::mutex mu;
   static std::map<Key, unsigned> cache;
-  static int cus = 0;
+  const int cus = (int)device_cus();
   const Key k{reinterpret_cast<const void*>(f), threads, lds};
   std::lock_guard<std::mutex> g(mu);
   auto it = cache.find(k);
   if (it != cache.end()) return it->second;
-  int dev = 0, per_cu = 0;
-  if (cus == 0 && (hipGetDevice(&dev) != hipSuccess ||
-                   hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess))
-    cus = 0;
+  int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, (int)threads, lds) != hipSuccess) per_cu = 0;
   const unsigned r = cus > 0 && per_cu > 0 ? (unsigned)(per_cu * cus) : 0u;  // 0: unknown
   cache[k] = r;
@@ -5791,7 +5800,8 @@ static void launch_maint_p(MaintKernel which, const Index& ix, const MaintArgs& 
       break;
     case MK_REFINE:
       hipLaunchKernelGGL(k_refine<P>, resident_grid(k_refine<P>, grid, blk, lds, sh), blk, lds, s, ix, a);
-      hipLaunchKernelGGL(k_refine_publish, dim3(std::min(persist_grid(a.n, RP_WAVES), PERSIST_BLOCKS / 4)),
+      hipLaunchKernelGGL(k_refine_publish,
+                         resident_grid(k_refine_publish, persist_grid(a.n, RP_WAVES), dim3(64 * RP_WAVES), 512u * RP_WAVES, sh),
                          dim3(64 * RP_WAVES), 512u * RP_WAVES, s, ix, a);
       break;
     case MK_REPAIR:
@@ -5916,9 +5926,11 @@ hipError_t launch_dirty(const Index& ix, uint64_t n_ids, Dyn d, uint32_t* dirty,
 hipError_t launch_compact(const Index& ix, const uint32_t* dirty, uint64_t n, Dyn d, hipStream_t s) {
   if (n == 0) return hipSuccess;
   const uint32_t per_wave = 512;
-  const unsigned blocks = persist_grid(n, COMPACT_WAVES);
-  hipLaunchKernelGGL(k_compact, dim3(std::min(blocks, PERSIST_BLOCKS / 4)), dim3(64 * COMPACT_WAVES),
-                     COMPACT_WAVES * per_wave, s, ix, dirty, n, d, per_wave);
+  const dim3 blk(64 * COMPACT_WAVES);
+  const size_t lds = COMPACT_WAVES * per_wave;
+  const unsigned sh = ix.concurrent ? 2u : 1u;
+  hipLaunchKernelGGL(k_compact, resident_grid(k_compact, persist_grid(n, COMPACT_WAVES), blk, lds, sh), blk, lds, s, ix, dirty,
+                     n, d, per_wave);
   return hipGetLastError();
 }
 

@@ -96,6 +96,7 @@ struct MaintArgs {
 
 enum MaintKernel { MK_FORWARD = 0, MK_REVERSE = 1, MK_REFINE = 2, MK_REPAIR = 3, MK_REVERSE_FAST = 4 };
 
+unsigned device_cus();
 hipError_t launch_init(const Index& ix, hipStream_t s);
 hipError_t launch_recycle(const Index& ix, hipStream_t s);
 // round control: counts (device array, or the host values when null), gate
