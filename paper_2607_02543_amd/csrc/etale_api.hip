@@ -8,6 +8,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <thread>
 #include <type_traits>
@@ -787,9 +788,13 @@ etale_status etale_create(const etale_config* cfg, etale_t* out) {
   Index& d = ix->dev;
   d.dim = c.dim;
   d.R = c.R;
-  d.a2 = c.alpha_num * c.alpha_num;
-  d.b2 = c.alpha_den * c.alpha_den;
   {
+    // uint8 rows: the test a^2 D1 <= b^2 D2 is exact in integers, so alpha in its
+    // lowest terms decides the same and takes the narrower products (12/10 as 6/5);
+    // float products would round differently
+    const uint32_t g = c.metric == ETALE_METRIC_L2_U8 ? std::gcd(c.alpha_num, c.alpha_den) : 1u;
+    d.a2 = (c.alpha_num / g) * (c.alpha_num / g);
+    d.b2 = (c.alpha_den / g) * (c.alpha_den / g);
     const uint64_t dmax = (uint64_t)c.dim * 255u * 255u;  // largest uint8 squared distance
     d.cmp32 = c.metric == ETALE_METRIC_L2_U8 && dmax < (1ull << 24) && d.a2 < (1u << 24) && d.b2 < (1u << 24) &&
               (uint64_t)std::max(d.a2, d.b2) * dmax < (1ull << 32);

@@ -88,3 +88,35 @@ def test_many_covered_pairs_cost_what_few_do():
     few, many = us((2, 1)), us((1, 1))
     print(f"[repair] few covered pairs {few:.0f} us, many {many:.0f} us", flush=True)
     assert many < 1.6 * few  # going through them one by one takes two and a half times as long
+
+
+def test_alpha_counts_in_its_lowest_terms():
+    import torch
+    from paper_2607_02543_amd import etale
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    x = torch.randint(0, 256, (20_000, 64), dtype=torch.uint8, device="cuda", generator=gen)
+
+    def churn(alpha):
+        g = etale.Index(64, R=32, L_build=64, n_entry=1024, id_capacity=20_000, slab_capacity=200_000, max_batch=2000,
+                        alpha=alpha, W=2)
+        for b in range(0, 20_000, 2000):
+            g.insert(x[b:b + 2000])
+        best = 1e9
+        for b in range(0, 6000, 1000):
+            ids = torch.arange(b, b + 1000, dtype=torch.int32, device="cuda")
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            g.delete(ids)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        e = g.export()
+        g.close()
+        return best * 1e6, e["nbr"], e["rho"]
+
+    low = churn((6, 5))
+    for alpha in ((12, 10), (600, 500)):
+        got = churn(alpha)
+        print(f"[alpha] 6/5 {low[0]:.0f} us, {alpha[0]}/{alpha[1]} {got[0]:.0f} us", flush=True)
+        assert np.array_equal(low[1], got[1]) and np.array_equal(low[2], got[2])
+        assert got[0] < 1.6 * low[0]  # the kernels for wide products take twice as long
