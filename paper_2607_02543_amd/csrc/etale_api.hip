@@ -782,6 +782,7 @@ etale_status etale_create(const etale_config* cfg, etale_t* out) {
   ALLOC(ix->far.id, far * 8);
   ALLOC(ix->far.mark, far * 8);
   ix->far.mask = (uint32_t)(far - 1);
+  ix->far.span = c.max_batch;
   ALLOC(ix->tcnt, C * 4);
   ALLOC(ix->status, 16);
 #undef ALLOC

@@ -3347,8 +3347,12 @@ __global__ void __launch_bounds__(256) k_set_lists(Index ix, MaintArgs a, const 
 // earlier calls count as empty. 65,536 distinct ids never handed out: 5,270 us
 // with a search of the positions before for each, 140 now (as many ids that
 // were handed out: the same).
-__device__ inline unsigned long long del_mark(const Index& ix, uint32_t t) {
-  return (ix.ctr[C_EPOCH] << 32) | (0xFFFFFFFFull - t);
+// A call's marks are the next max_batch numbers, the first position's the largest
+// (2^64 / max_batch calls: with a position's 32 bits beside it the epoch would
+// start over after 2^32 rounds, days of small ones, and an id that a refused call
+// had named could no longer be deleted)
+__device__ inline unsigned long long del_mark(const Index& ix, const FarMarks& f, uint32_t t) {
+  return ix.ctr[C_EPOCH] * f.span + (f.span - 1u - t);
 }
 
 __device__ inline unsigned long long* del_mark_word(const Index& ix, const FarMarks& f, uint32_t id) {
@@ -3377,7 +3381,7 @@ __global__ void __launch_bounds__(256) k_del_mark(Index ix, FarMarks f, const ui
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n) return;
   unsigned long long* const w = del_mark_word(ix, f, ids[t]);
-  const unsigned long long mark = del_mark(ix, t);
+  const unsigned long long mark = del_mark(ix, f, t);
   // many repeats of one id: those that come later leave its word alone (65,536:
   // 870 -> 210 us; in a short list the read costs more than the atomics it saves)
   if (n <= 4096u || __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < mark) atomicMax(w, mark);
@@ -3397,7 +3401,7 @@ __global__ void __launch_bounds__(256) k_del_classify(Index ix, FarMarks f, cons
   if (t < n) {
     const uint32_t id = ids[t];
     uint8_t st = DEL_OK;
-    if (*del_mark_word(ix, f, id) != del_mark(ix, t)) {
+    if (*del_mark_word(ix, f, id) != del_mark(ix, f, t)) {
       st = DEL_DUPLICATE;
     } else if ((uint64_t)id >= ix.ctr[C_NEXT_ID]) {
       st = DEL_OUT_OF_RANGE;

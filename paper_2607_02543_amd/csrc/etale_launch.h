@@ -151,6 +151,7 @@ struct FarMarks {
   unsigned long long* id = nullptr;
   unsigned long long* mark = nullptr;
   uint32_t mask = 0;  // slots less one: a power of two of at least twice max_batch
+  uint32_t span = 1;  // marks of one call: max_batch of them
 };
 hipError_t launch_far_init(const FarMarks& f, hipStream_t s);
 hipError_t launch_del_mark(const Index& ix, const FarMarks& f, const uint32_t* ids, uint32_t n, Dyn d, hipStream_t s);
