@@ -85,3 +85,36 @@ def test_infinities_and_nans_rank_by_the_rows_own_distance(dim):
     assert np.array_equal(got, np.take_along_axis(d, want, axis=1))
     assert np.array_equal(i, want)
     g.close()
+
+
+# with every row in the entry set a search starts from its exact nearest rows: tiles of three sizes, the selection from
+# registers, from group minima and the general one. Values in eighths, so that every finite sum is exact
+@pytest.mark.parametrize("dim,n,nq", [(96, 700, 20), (96, 4200, 1100), (192, 260, 300), (768, 300, 33)])
+def test_start_lists_with_infinities_and_nans(dim, n, nq):
+    from paper_2607_02543_amd import etale
+    rng = np.random.default_rng(n + dim)
+    x = (rng.integers(-2, 3, (n, dim)) / 8).astype(np.float32)
+    q = (rng.integers(-2, 3, (nq, dim)) / 8).astype(np.float32)
+    q[q == 0] = 0.125
+    for v in (np.inf, -np.inf, np.nan):
+        at = rng.choice(n, 8, replace=False)
+        x[at, rng.integers(0, dim, 8)] = v
+    q[3, 5], q[4, 6] = np.inf, -np.inf
+    g = etale.Index(dim, R=8, L_build=16, n_entry=n, id_capacity=n, slab_capacity=30 * n, max_batch=n, metric=etale.METRIC_IP_F32)
+    g.insert(_up(x))
+    with np.errstate(invalid="ignore"):
+        d = (1 - np.stack([(x.astype(np.float64) * r.astype(np.float64)).sum(1) for r in q])).astype(np.float32)
+    # a row's own NaN is positive and its distance negative: before every other. A NaN of the hardware's own making (an
+    # infinite component of the query on a zero) is negative and its distance positive: after every other
+    own = np.isnan(x).any(1)
+    place = np.where(own[None, :], 0, np.where(np.isnan(d), 2, 1))
+    want = np.stack([np.lexsort((np.arange(n), np.nan_to_num(r, nan=0.0, posinf=np.inf, neginf=-np.inf), c))[:10]
+                     for r, c in zip(d, place)])
+    for L in (16, 64, 128, 200):
+        i, got = g.search(_up(q), 10, L)
+        assert np.array_equal(i.cpu().numpy(), want), L
+        assert np.array_equal(got.cpu().numpy(), np.take_along_axis(d, want, axis=1), equal_nan=True), L
+    finite = np.isfinite(q).all(1)  # with both kinds of NaN in a row's sum its lanes' order decides
+    i, got = g.bruteforce(_up(q[finite]), 10)
+    assert np.array_equal(i.cpu().numpy(), want[finite])
+    g.close()
