@@ -2350,8 +2350,8 @@ __device__ inline uint64_t repair_pair(const Index& ix, const MaintArgs& a, uint
 // counter per id counts a target's pairs as they are generated (a pair's count is
 // its arrival rank, and the first one puts the target on a list), the listed
 // counts become places, the pairs go to their target's place by rank, and each
-// run is put in source order on its own (most have one or two pairs). Four
-// launches, where three passes of a radix sort by target and the search for run
+// run is put in source order on its own (most have one or two pairs; hubs, and
+// every node while an index is small, have more). Four launches, where three passes of a radix sort by target and the search for run
 // starts took eleven, of 4-7 us each at any size. With the deletes marked in
 // place instead of sorted, a round's pass: 10k rows, 100 + 100, 586 -> 497 us;
 // 200k, 2,000 + 2,000, 1,204 -> 1,110; 1M, 10,000 + 10,000, 2,880 -> 2,835.
@@ -3073,8 +3073,6 @@ __global__ void __launch_bounds__(256) k_reverse_apply(Index ix, MaintArgs a) {
   finish_slabs_block(ix, cur, C_PUB_REVERSE);
 }
 
-// the same with the cached candidate state (uint8 rows, R <= 32): a kernel of
-// its own so that its registers are not those of the generic path
 // Reverse edges in the concurrent mode (Algorithm 2's loop as the paper runs
 // it): the (target, source) offers are not sorted or grouped; each wave takes
 // single offers and applies each to the target's list as it stands, with a
@@ -3163,7 +3161,9 @@ struct LaunchSlabs {
   }
 };
 
-// with a.slow: the targets k_reverse_cover left, by run index
+// k_reverse_apply with the cached candidate state (uint8 rows, R <= 32): a kernel
+// of its own so that its registers are not those of the generic path. With a.slow:
+// the targets k_reverse_cover left, by run index
 template <int G>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) k_reverse_chain(Index ix, MaintArgs a) {
   extern __shared__ __align__(16) char smem[];
@@ -5252,9 +5252,9 @@ __global__ void __launch_bounds__(64) k_bruteforce_f32(Index ix, const float* q,
 // and the query's come as scalars, so nothing but the FMAs is left in the loop;
 // sums that wait for their pair (rows past 96 elements) and the keys, which are
 // reduced 16 bytes at a time, are in LDS. 1,000 queries on 100,003 x 96-d rows:
-// 2.75 ms with one wave per query reading all rows (1,000 waves for the chip),
-// 0.43 ms now (first pass 346 us, 28 T FMA/s of the 39 that unpacked FP32
-// reaches; second pass 64 us).
+// 4.44 ms with one wave per query reading all rows two at a time per lane group
+// (1,000 waves for the chip; 2.75 ms with eight at a time), 0.43 ms now (first
+// pass 346 us, 28 T FMA/s of the 39 that unpacked FP32 reaches; second pass 64 us).
 constexpr int BF_WAVES = 4;                        // groups per workgroup, all with the same queries
 template <int G> constexpr int bf_queries() { return G <= 16 ? 32 : 16; }  // and how many of those
 template <int G> constexpr int bf_levels() { return G <= 16 ? 1 : G == 32 ? 2 : 3; }  // log2(G / 8) waiting sums
